@@ -963,12 +963,13 @@ def mfma_ceiling(ms=20.0):
 def mfma_instruction(kernel):
     """The MFMA instruction a gemm_mfma_kernel<GemmShape<NW, WM, WN, TM, TN,
     STAGES, BK>> issues: v_mfma_f32_16x16x32_bf16 where its tile has 256
-    columns (WM TM 32) or 256 tokens (WN TN 32) and 64-row k-tiles, else
-    v_mfma_f32_32x32x16_bf16."""
+    columns (WM TM 32) or 256 tokens (WN TN 32) and 64-row k-tiles, and in
+    the streaming tiles (BK = 128), else v_mfma_f32_32x32x16_bf16."""
     if "GemmShape<" not in kernel:
         return "32x32x16"
     nw, wm, wn, tm, tn, stages, bk = [int(v) for v in kernel.split("GemmShape<")[1].split(">")[0].split(",")[:7]]
-    return "16x16x32" if bk == 64 and (wm * tm * 32 >= 256 or wn * tn * 32 >= 256) else "32x32x16"
+    large = bk == 64 and (wm * tm * 32 >= 256 or wn * tn * 32 >= 256)
+    return "16x16x32" if large or bk == 128 else "32x32x16"
 
 
 def run_suite(args):

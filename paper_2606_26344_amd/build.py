@@ -36,6 +36,10 @@ FLAGS = [
     "-Wextra",
     "-Werror",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # MFMA results in VGPRs wherever they fit: with the default choice the
+    # register allocator moves the streaming kernels' accumulators between the
+    # two halves of the register file in every k step.
+    "-mllvm", "-amdgpu-mfma-vgpr-form=1",
     "-I", INCLUDE,
     "-I", CSRC,
 ]

@@ -55,40 +55,11 @@
 #include <utility>
 
 #include "common.hpp"
+#include "gemm_params.hpp"
+#include "gemm_stream.hpp"
 #include "tiling.hpp"
 
 namespace gmlp {
-
-struct GemmParams {
-    const uint16_t *w0;  // [K, M] bf16, M contiguous (Wg, or Wd)
-    const uint16_t *w1;  // [K, M] bf16 second weight (Wu) of the dual kernel
-    const uint16_t *act; // [N, K] bf16, K contiguous (X, or H)
-    uint16_t *out;       // [N, M] bf16 (H, or Y)
-    float *partial;      // split-K partial sums, fp32, [split][tile of the launch][wave][piece][lane]
-    uint32_t *counters;  // split-K arrival counter per output tile (zero on entry and exit)
-    int M, N, K;
-    int k_split; // K rows per split (a multiple of BK when splits > 1)
-    int splits;
-    int tiles_m, tiles_n;
-    int group_m; // consecutive blocks sweep group_m column tiles before the next token tile
-    // This launch computes tiles [tile_base, tile_base + tile_count) of the
-    // block order of all tiles_m x tiles_n tiles (a plan can give the tiles
-    // of a last, partial round of blocks to a split-K part of their own).
-    int tile_base, tile_count;
-    // A split-K launch may start with head_blocks blocks (a multiple of 8)
-    // that each compute one whole tile over all of K: tiles [0, head_blocks)
-    // of the block order, before its split tiles, so those start as soon as
-    // CUs free up instead of after the last whole tile.
-    int head_blocks;
-    // Gate/up epilogue: activation (enum Activation), swish slope, and the
-    // per-token RMSNorm scales [N] (nullptr: none).
-    int activation;
-    float beta;
-    const float *rrms;
-    // Store epilogue: per-token divisors [N] (nullptr: none).  Softmax+MatMul
-    // divides its result rows by the softmax sums here.
-    const float *rowdiv;
-};
 
 // Physical 16-byte chunk of logical chunk c in row k of a weight tile.  The
 // XOR keeps the 4 rows x 4 chunks read by 32 lanes of one transposing load
@@ -818,28 +789,33 @@ __device__ __forceinline__ int gemm_block(const GemmParams &p, int block, StageP
 template <class S, int EPI, bool SPLIT, bool STREAM_W>
 __global__ __launch_bounds__(S::NTHREADS, 1) void gemm_mfma_kernel(GemmParams p)
 {
-    constexpr int STAGES = S::STAGES;
-    // One LDS array per pipeline stage: distinct objects let the compiler see
-    // that reading one stage does not depend on the DMA into another.
-    __shared__ __attribute__((aligned(1024))) uint8_t lds0[S::STAGE_BYTES];
-    __shared__ __attribute__((aligned(1024))) uint8_t lds1[S::STAGE_BYTES];
-    __shared__ __attribute__((aligned(1024))) uint8_t lds2[STAGES > 2 ? S::STAGE_BYTES : 16];
-    __shared__ __attribute__((aligned(1024))) uint8_t lds3[STAGES > 3 ? S::STAGE_BYTES : 16];
-    __shared__ __attribute__((aligned(1024))) uint8_t lds4[STAGES > 4 ? S::STAGE_BYTES : 16];
-    __shared__ __attribute__((aligned(1024))) uint8_t lds5[STAGES > 5 ? S::STAGE_BYTES : 16];
-    __shared__ __attribute__((aligned(1024))) uint8_t lds6[STAGES > 6 ? S::STAGE_BYTES : 16];
-    __shared__ __attribute__((aligned(1024))) uint8_t lds7[STAGES > 7 ? S::STAGE_BYTES : 16];
-    auto stage_ptr = [&](auto s) __attribute__((always_inline)) -> uint8_t * {
-        if constexpr (decltype(s)::value == 0) return lds0;
-        else if constexpr (decltype(s)::value == 1) return lds1;
-        else if constexpr (decltype(s)::value == 2) return lds2;
-        else if constexpr (decltype(s)::value == 3) return lds3;
-        else if constexpr (decltype(s)::value == 4) return lds4;
-        else if constexpr (decltype(s)::value == 5) return lds5;
-        else if constexpr (decltype(s)::value == 6) return lds6;
-        else return lds7;
-    };
-    gemm_block<S, EPI, SPLIT, STREAM_W>(p, blockIdx.x, stage_ptr);
+    if constexpr (S::BK == 128) {
+        static_assert(SPLIT && STREAM_W, "one token tile, each weight read once");
+        stream_block<S, EPI>(p);
+    } else {
+        constexpr int STAGES = S::STAGES;
+        // One LDS array per pipeline stage: distinct objects let the compiler see
+        // that reading one stage does not depend on the DMA into another.
+        __shared__ __attribute__((aligned(1024))) uint8_t lds0[S::STAGE_BYTES];
+        __shared__ __attribute__((aligned(1024))) uint8_t lds1[S::STAGE_BYTES];
+        __shared__ __attribute__((aligned(1024))) uint8_t lds2[STAGES > 2 ? S::STAGE_BYTES : 16];
+        __shared__ __attribute__((aligned(1024))) uint8_t lds3[STAGES > 3 ? S::STAGE_BYTES : 16];
+        __shared__ __attribute__((aligned(1024))) uint8_t lds4[STAGES > 4 ? S::STAGE_BYTES : 16];
+        __shared__ __attribute__((aligned(1024))) uint8_t lds5[STAGES > 5 ? S::STAGE_BYTES : 16];
+        __shared__ __attribute__((aligned(1024))) uint8_t lds6[STAGES > 6 ? S::STAGE_BYTES : 16];
+        __shared__ __attribute__((aligned(1024))) uint8_t lds7[STAGES > 7 ? S::STAGE_BYTES : 16];
+        auto stage_ptr = [&](auto s) __attribute__((always_inline)) -> uint8_t * {
+            if constexpr (decltype(s)::value == 0) return lds0;
+            else if constexpr (decltype(s)::value == 1) return lds1;
+            else if constexpr (decltype(s)::value == 2) return lds2;
+            else if constexpr (decltype(s)::value == 3) return lds3;
+            else if constexpr (decltype(s)::value == 4) return lds4;
+            else if constexpr (decltype(s)::value == 5) return lds5;
+            else if constexpr (decltype(s)::value == 6) return lds6;
+            else return lds7;
+        };
+        gemm_block<S, EPI, SPLIT, STREAM_W>(p, blockIdx.x, stage_ptr);
+    }
 }
 
 } // namespace gmlp

@@ -205,6 +205,11 @@ int run_gate_up(const Step &s, const void *X, const void *Wg, const void *Wu, vo
         if (s.N <= PairMid160::BN)
             return launch_gemm<PairMid160, EPI_GATE_PAIR, true, true>(s, Wg, Wu, X, H, ws, l, v, rrms, nullptr, st);
         return launch_gemm<PairMid192, EPI_GATE_PAIR, true, true>(s, Wg, Wu, X, H, ws, l, v, rrms, nullptr, st);
+    case K_STREAM_GU:
+        return with_stream_tile(s, [&](auto tn, auto wm) {
+            return launch_gemm<StreamGateUp<decltype(tn)::value, decltype(wm)::value>, EPI_GATE_MUL, true, true>(
+                s, Wg, Wu, X, H, ws, l, v, rrms, nullptr, st);
+        });
     case K_GEMV:
         return v.rms ? launch_gemv<2, EPI_GATE_MUL, true>(s, Wg, Wu, X, H, ws, l, v, st)
                      : launch_gemv<2, EPI_GATE_MUL, false>(s, Wg, Wu, X, H, ws, l, v, st);
@@ -262,6 +267,11 @@ int run_down(const Step &s, const void *H, const void *Wd, void *Y, uint8_t *ws,
                                                                                    nullptr, rowdiv, st);
     case K_GEMM_DN_W: // one token tile: always streamed
         return launch_gemm<DownMid96, EPI_STORE, true, true>(s, Wd, nullptr, H, Y, ws, l, plain, nullptr, rowdiv, st);
+    case K_STREAM_DN:
+        return with_stream_tile(s, [&](auto tn, auto wm) {
+            return launch_gemm<StreamDown<decltype(tn)::value, decltype(wm)::value>, EPI_STORE, true, true>(
+                s, Wd, nullptr, H, Y, ws, l, plain, nullptr, rowdiv, st);
+        });
     case K_GEMV: return launch_gemv<1, EPI_STORE, false>(s, Wd, nullptr, H, Y, ws, l, plain, st, rowdiv);
     default: return fail(GMLP_ERR_INVALID_ARG, "no down kernel for this plan");
     }

@@ -139,6 +139,7 @@ enum Kind {
     K_NONE,
     K_GEMM_GU_L, K_GEMM_GU_S, K_GEMM_GU_W, K_GEMM_GU_M, K_GEMM_GU_T, K_GEMM_GU_P, K_GEMM_GU_Y,
     K_GEMM_DN_L, K_GEMM_DN_S, K_GEMM_DN_W, K_GEMM_DN_M, K_GEMM_DN_T, K_GEMM_DN_X, K_GEMM_DN_Y, K_GEMM_DN_Q,
+    K_STREAM_GU, K_STREAM_DN,
     K_GEMV
 };
 
@@ -149,6 +150,7 @@ struct Step {
     int tiles_m = 0, tiles_n = 0; // GEMM
     int group_m = 1;              // GEMM block order
     int strips = 0;               // GEMV
+    int stream_wm = 4;            // streaming tiles: columns / 32
     int strip_lanes = 32;         // GEMV: 8-column lanes per row
     int counter_stride = 1;       // GEMV: words between two strips' arrival counters
     int splits = 1, k_split = 0;
@@ -229,7 +231,8 @@ void choose_splits(Step &s, int tiles, int target, int tile_k, int min_tiles)
 }
 
 template <class S>
-void gemm_step(Step &s, Kind kind, int M, int N, int K, int nw, bool allow_split, int group_m)
+void gemm_step(Step &s, Kind kind, int M, int N, int K, int nw, bool allow_split, int group_m,
+               int min_k_tiles = 2)
 {
     s.kind = kind;
     s.M = M;
@@ -244,7 +247,7 @@ void gemm_step(Step &s, Kind kind, int M, int N, int K, int nw, bool allow_split
     s.tail_splits = 1;
     s.tail_k_split = 0;
     if (allow_split)
-        choose_splits(s, tiles, kBlockTarget, S::BK, 2);
+        choose_splits(s, tiles, kBlockTarget, S::BK, min_k_tiles);
     else {
         s.splits = 1;
         s.k_split = K;
@@ -310,6 +313,81 @@ void pair_step(Step &s, int M, int N, int K, int group_m)
     s.threads = S::NTHREADS;
     s.counters = tiles;
     s.partial_bytes = (size_t)2 * tiles * S::BMW * S::BN * sizeof(float);
+}
+
+// The streaming tiles (gemm_stream.hpp), one token tile of 32 TN tokens and
+// 32 WM columns per weight: 128 columns with one unit (32 rows of a weight)
+// in flight per wave, 64 columns with two, so that a block keeps 32 KB in
+// flight (the weight stream alone, 117 MB on 224 blocks: 6.2 TB/s with 32 KB
+// in flight per block, 5.7 with 64, 5.6 with 128).
+template <int TN, int WM>
+using StreamGateUp = GemmShape<2, WM, 1, 1, TN, WM == 4 ? 1 : 2, 128>;
+template <int TN, int WM>
+using StreamDown = GemmShape<1, WM, 1, 1, TN, WM == 4 ? 1 : 2, 128>;
+constexpr int kStreamMaxTokens = 128;
+constexpr int kStreamWideTokens = 16; // the 128-column tiles: one 16-token tile
+
+// Which streaming tile (WM) a step of n tokens and an M x K weight takes on
+// the automatic path, 0: the LDS-ring tiles.  With small weights a step is
+// bound by its latency: the ring's barriers and above all the split-K
+// exchange, whose last block reads (splits x columns) of fp32, four times
+// less with 64-column tiles.  With large weights the 64-column tiles' 128-byte
+// row segments stream at 5.5 TB/s against 6.4, and the token fragments, which
+// the streaming kernel reads 16 rows at a time, cost more than the ring's
+// rows (T = 128 at D = 4096, F = 14336: gate/up 80 us against 57.7).
+// Measured, ring against streaming, us:
+//   down     D = 1024, F = 4096: T = 8 21.9 -> 9.6, 48 25.8 -> 10.7, 128 32.7 ->
+//            18.6; D = 2048, F = 8192: T = 24 18.5 -> 13.0, 51 21.8 -> 15.6,
+//            128 27.8 -> 25.0; D = 3072, F = 8192: T = 96 23.9 -> 25.6 (kept)
+//   gate/up  D = 1024, F = 4096: T = 8 15.5 -> 10.6, 48 20.8 -> 12.5, 128 30.2 ->
+//            19.7; D = 2048, F = 8192: T = 51 24.1 -> 22.4, 128 31.6 -> 29.0;
+//            D = 3072, F = 8192: T = 64 29.2 -> 29.6 (kept)
+// Up to 16 tokens the 128-column tiles also beat the ring at larger weights:
+// down D = 2048, F = 8192 18.4 -> 12.8, D = 3072, F = 8192 17.9 -> 14.5,
+// D = 4096, F = 14336 25.8 -> 23.8, D = 8192, F = 28672 82.7 -> 82.0 (kept);
+// gate/up 20.9 -> 18.0, 25.4 -> 23.3, D = 4096, F = 11008 35.6 -> 35.7 (kept).
+// Gate/up steps of more than 96 128-column tiles keep the ring (pairs above
+// 64 tokens): they fill the chip without splits shorter than half of K.
+int stream_width(int64_t n, int64_t M, int64_t K, bool gate_up)
+{
+    if (n > kStreamMaxTokens || (gate_up && cdiv(M, 128) >= (kPairMinBlocks + 1) / 2))
+        return 0;
+    const int64_t weight = M * K;
+    if (n <= kStreamWideTokens && weight > (int64_t(1) << 22))
+        return weight <= (gate_up ? int64_t(3) << 23 : int64_t(1) << 26) ? 4 : 0;
+    return weight <= (int64_t(1) << 24) ? 2 : 0;
+}
+
+// f(TN, WM) as integral constants, for the streaming tile of a step.
+template <class F>
+auto with_stream_tile(const Step &s, F f)
+{
+    using std::integral_constant;
+    if (s.stream_wm == 4)
+        return f(integral_constant<int, 1>{}, integral_constant<int, 4>{});
+    switch ((s.N + 31) / 32) {
+    case 1: return f(integral_constant<int, 1>{}, integral_constant<int, 2>{});
+    case 2: return f(integral_constant<int, 2>{}, integral_constant<int, 2>{});
+    case 3: return f(integral_constant<int, 3>{}, integral_constant<int, 2>{});
+    default: return f(integral_constant<int, 4>{}, integral_constant<int, 2>{});
+    }
+}
+
+// Splits of the 64-column tiles keep at least 512 rows (measured at
+// D = 1024, F = 4096, T = 64, splits of 256 rows against 512: down 14.3 -> 11.5
+// us, gate/up 14.8 -> 13.7), those of the 128-column tiles 256.
+void stream_step(Step &s, int wm, int M, int N, int K, bool gate_up)
+{
+    s.stream_wm = wm;
+    s.N = N;
+    with_stream_tile(s, [&](auto tn, auto w) {
+        constexpr int TN = decltype(tn)::value, WM = decltype(w)::value;
+        constexpr int min_k_tiles = WM == 4 ? 2 : 4;
+        if (gate_up)
+            gemm_step<StreamGateUp<TN, WM>>(s, K_STREAM_GU, M, N, K, 2, true, 1, min_k_tiles);
+        else
+            gemm_step<StreamDown<TN, WM>>(s, K_STREAM_DN, M, N, K, 1, true, 1, min_k_tiles);
+    });
 }
 
 // Rows per load batch of all row groups of a block, per token count and
@@ -505,6 +583,12 @@ Plan make_plan(int64_t T, int64_t D, int64_t F, int path)
         gemm_step<DownMid192>(p.down, K_GEMM_DN_Y, (int)D, (int)T, (int)F, 1, true, kGroupDown);
     else
         gemm_step<DownSmall>(p.down, K_GEMM_DN_S, (int)D, (int)T, (int)F, 1, true, kGroupDown);
+    if (asked == GMLP_PATH_AUTO) {
+        if (const int wm = stream_width(T, F, D, true))
+            stream_step(p.gate_up, wm, (int)F, (int)T, (int)D, true);
+        if (const int wm = stream_width(T, D, F, false))
+            stream_step(p.down, wm, (int)D, (int)T, (int)F, false);
+    }
     // 257 to 384 tokens: two 192-token down tiles split over K where there
     // are 64 to 128 of them (so that at least two splits fill a round) and
     // a block's work is at most 95% of what the rules above give it.
@@ -568,7 +652,7 @@ Layout make_layout(int64_t T, int64_t D, int64_t F)
     T = std::max<int64_t>(T, 1);
     int counters = 0;
     size_t partial = 0;
-    for (int path : {GMLP_PATH_GEMV, GMLP_PATH_MFMA}) {
+    for (int path : {GMLP_PATH_AUTO, GMLP_PATH_GEMV, GMLP_PATH_MFMA}) {
         if (path == GMLP_PATH_GEMV && T > kGemvMaxTokens)
             continue;
         const Plan p = make_plan(T, D, F, path);
@@ -748,6 +832,14 @@ std::string kernel_name(const Step &s, bool gate_up)
                                                          : shape_name<PairMid192>();
         return "gemm_mfma_kernel<" + shape + ", 2, true, true>";
     }
+    case K_STREAM_GU:
+    case K_STREAM_DN:
+        return with_stream_tile(s, [&](auto tn, auto wm) {
+            constexpr int TN = decltype(tn)::value, WM = decltype(wm)::value;
+            return "gemm_mfma_kernel<" +
+                   (gate_up ? shape_name<StreamGateUp<TN, WM>>() + ", 0" : shape_name<StreamDown<TN, WM>>() + ", 1") +
+                   ", true, true>";
+        });
     case K_GEMV:
         return "gemv_splitk_kernel<" + std::to_string(s.N) + (gate_up ? ", 2, 0, false>" : ", 1, 1, false>");
     default: return "none";
@@ -843,8 +935,8 @@ int check_smm_args(const void *X, const void *Y, const void *Z, int64_t M, int64
 // Gated MLP's pair of steps.
 Step smm_matmul_step(int64_t M, int64_t K, int64_t N, int path)
 {
-    if (path == GMLP_PATH_AUTO)
-        path = M <= kGemvMaxTokens ? GMLP_PATH_GEMV : GMLP_PATH_MFMA;
+    if (path == GMLP_PATH_AUTO && M <= kGemvMaxTokens)
+        path = GMLP_PATH_GEMV;
     return make_plan(M, N, K, path).down;
 }
 
@@ -856,7 +948,7 @@ Layout smm_layout(int64_t M, int64_t K, int64_t N)
     M = std::max<int64_t>(M, 1); // as for make_layout: M = 0 launches nothing
     int counters = 0;
     size_t partial = 0;
-    for (int path : {GMLP_PATH_GEMV, GMLP_PATH_MFMA}) {
+    for (int path : {GMLP_PATH_AUTO, GMLP_PATH_GEMV, GMLP_PATH_MFMA}) {
         if (path == GMLP_PATH_GEMV && M > kGemvMaxTokens)
             continue;
         const Step s = smm_matmul_step(M, K, N, path);

@@ -1,0 +1,119 @@
+"""The streaming MFMA kernels (6 to 128 tokens, small weights) against the
+oracle and against the LDS-ring kernels of the explicit "mfma" path, at the
+edges of their tiles: 16-token tiles (15 .. 17, ... 112, 113, 128 tokens), 64-
+and 128-column tiles cut short by F or D, K tails shorter than a 32-row batch,
+one split and many, waves without a batch (K = 8), and every epilogue.
+
+Both paths add the same bf16 products in fp32, in another order, and round
+once: an element differs by at most one bf16 step (2^-8 of its value) plus,
+after the down step, what single-step differences of H give (2^-8 of H's rms
+over many terms); the oracle's rule |got - ref| <= 1e-2 (|ref| + rms) covers
+both, and is asserted for either reference.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2606_26344_amd import gmlp
+from paper_2606_26344_amd import inputs as I
+from paper_2606_26344_amd import softmax_matmul as smm
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-2
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    assert torch.cuda.is_available(), "GPU tests need a HIP device"
+    gmlp.library()
+
+
+def _f64(t):
+    return I.bf16_bits_to_f32(gmlp.to_bf16_bits(t)).astype(np.float64)
+
+
+def _check(got, ref, what):
+    assert np.all(np.isfinite(got)), what
+    bound = TOL * (np.abs(ref) + np.sqrt(np.mean(ref ** 2)))
+    ratio = float(np.max(np.abs(got - ref) / bound))
+    print("%s max err/bound = %.3f" % (what, ratio), flush=True)
+    assert ratio <= 1.0, what
+
+
+def _is_stream(line):
+    return line[0].startswith("gemm_mfma_kernel<GemmShape<") and ", 128>" in line[0]
+
+
+# T, D, F: 64-column tiles in both steps unless noted.
+SHAPES = [(T, 264, 520) for T in (6, 15, 16, 17, 31, 32, 33, 48, 49, 64, 65, 80, 81, 96, 97, 112, 113, 128)]
+SHAPES += [(24, 8, 8), (7, 8, 1032), (40, 1032, 8), (128, 40, 72),   # waves without a batch, one short tile
+           (16, 2056, 3080), (9, 1032, 4104), (16, 3080, 2056),      # 128-column tiles (weights above 2^22), short last tile
+           (51, 1032, 4104), (100, 2056, 1544), (128, 1544, 4168),    # several splits, ragged K
+           (64, 4104, 264), (90, 136, 11000)]
+
+
+@pytest.mark.parametrize("T,D,F", SHAPES, ids=["T%dD%dF%d" % s for s in SHAPES])
+def test_stream_tiles(orc, T, D, F):
+    plan = gmlp.describe(T, D, F)
+    assert all(_is_stream(line) for line in plan), plan
+    X, Wg, Wu, Wd = I.generate(T, D, F, seed=T + D + F)
+    x, wg, wu, wd = (gmlp.from_bf16_bits(a) for a in (X, Wg, Wu, Wd))
+    ws = gmlp.Workspace(T, D, F)
+    h = gmlp.gate_up(x, wg, wu, workspace=ws)
+    y = gmlp.down(h, wd, workspace=ws)
+    y2 = gmlp.forward(x, wg, wu, wd, workspace=ws)
+    ring_h = gmlp.gate_up(x, wg, wu, path="mfma", workspace=ws)
+    ring_y = gmlp.down(h, wd, path="mfma", workspace=ws)
+    again = gmlp.forward(x, wg, wu, wd, workspace=ws)
+    torch.cuda.synchronize()
+    assert torch.equal(y.view(torch.int16), y2.view(torch.int16))
+    assert torch.equal(again.view(torch.int16), y2.view(torch.int16))
+    assert int(torch.count_nonzero(ws.buffer[:128 * 1024])) == 0  # counters back at zero
+    rows = np.arange(T) if T * D * F < 2 ** 27 else I.sample_rows(T, 24)
+    _, H_ref = orc.gated_mlp_rows(X, Wg, Wu, Wd, rows=rows, return_h=True)
+    what = "T=%d D=%d F=%d" % (T, D, F)
+    _check(_f64(h)[rows], H_ref, "H " + what)
+    _check(_f64(y)[rows], orc.down_rows(gmlp.to_bf16_bits(h)[rows], Wd), "Y " + what)
+    _check(_f64(h), _f64(ring_h), "H against the ring " + what)
+    _check(_f64(y), _f64(ring_y), "Y against the ring " + what)
+
+
+@pytest.mark.parametrize("T", [16, 40, 90, 128])
+@pytest.mark.parametrize("variant", [dict(rmsnorm=True, eps=1e-5), dict(activation="swish", beta=1.702, rmsnorm=True),
+                                     dict(activation="sigmoid")], ids=["rmsnorm", "rmsnorm_swiglu", "glu"])
+def test_stream_variants(orc, T, variant):
+    D, F = 520, 1032
+    X, Wg, Wu, Wd = I.generate(T, D, F, seed=T)
+    args = [gmlp.from_bf16_bits(a) for a in (X, Wg, Wu, Wd)]
+    assert all(_is_stream(line) for line in gmlp.describe(T, D, F))
+    y = gmlp.forward(*args, workspace=gmlp.Workspace(T, D, F), **variant)
+    torch.cuda.synchronize()
+    _check(_f64(y), orc.gated_mlp_rows(X, Wg, Wu, Wd, **variant), "T=%d %s" % (T, variant))
+
+
+@pytest.mark.parametrize("M,K,N", [(9, 520, 264), (33, 1032, 72), (100, 2056, 1032), (16, 4104, 1544), (128, 72, 520)])
+def test_stream_softmax_matmul(M, K, N):
+    assert _is_stream(smm.describe(M, K, N)[1])
+    X, Y = I.generate_softmax_matmul(M, K, N, seed=M)
+    z = smm.softmax_matmul(gmlp.from_bf16_bits(X), gmlp.from_bf16_bits(Y), workspace=smm.make_workspace(M, K, N))
+    torch.cuda.synchronize()
+    _check(_f64(z), oracle.softmax_matmul_rows(X, Y), "M=%d K=%d N=%d" % (M, K, N))
+
+
+@pytest.mark.parametrize("T", [16, 70])
+def test_stream_specials(T):
+    # A row with a NaN, a weight column with an infinity: each stays in its
+    # row and its column, also past the K tail and the token tail, where the
+    # kernel multiplies zeros.
+    D, F = 1032, 520
+    X, Wg, Wu, Wd = I.generate(T, D, F, seed=3)
+    Wd = Wd.copy()
+    H = I.f32_to_bf16_bits(np.abs(np.random.default_rng(1).standard_normal((T, F))).astype(np.float32) + 0.5)
+    Wd[F - 1, 5] = 0x7F80  # +inf
+    H[T - 1, F - 3] = 0x7FC0  # NaN
+    y = I.bf16_bits_to_f32(gmlp.to_bf16_bits(gmlp.down(gmlp.from_bf16_bits(H), gmlp.from_bf16_bits(Wd))))
+    assert np.all(np.isnan(y[T - 1]))
+    assert np.all(np.isposinf(y[:T - 1, 5]))
+    assert np.all(np.isfinite(np.delete(y[:T - 1], 5, axis=1)))
