@@ -59,7 +59,9 @@ enum gmlp_status {
 
 /* Which kernels compute the call (gmlp_forward_ex). */
 enum gmlp_path {
-    GMLP_PATH_AUTO = 0,  /* GEMV for T <= 5, MFMA GEMMs otherwise (measured faster from T = 6) */
+    GMLP_PATH_AUTO = 0,  /* GEMV for T <= 5, MFMA GEMMs otherwise (measured faster from T = 6;
+                            for small weights and T <= 128 tiles that stream the weights into
+                            registers, which the paths below do not run) */
     GMLP_PATH_GEMV = 1,  /* split-K streaming GEMV kernels; needs T <= 8 */
     GMLP_PATH_MFMA = 2,  /* MFMA GEMM kernels (any T) */
     GMLP_PATH_FUSED = 3, /* the whole MLP in one GEMV kernel: the first blocks run the gate/up
@@ -76,6 +78,17 @@ enum gmlp_path {
                                  two-kernel GMLP_PATH_MFMA plan of the 32- and 64-token tiles, bit
                                  for bit.  Only for gmlp_forward_ex / gmlp_forward_variant. */
 };
+
+/*
+ * Or'ed into GMLP_PATH_AUTO, GMLP_PATH_GEMV or GMLP_PATH_MFMA of an entry
+ * point that takes a path and a workspace (except softmax_matmul_divide_ws):
+ * the workspace's counter block has not been prepared (gmlp_workspace_init),
+ * its contents may be anything.  The call clears the counters its kernels use
+ * first, with a kernel of its own or in its first kernel, and not at all where
+ * none are used.  Such a call does not prepare the workspace for calls without
+ * the flag.  For scratch memory that is taken for one call.
+ */
+#define GMLP_FRESH_WORKSPACE 256
 
 /*
  * Gate activations of the Gated MLP family, H = act(X Wg) * (X Wu).  The

@@ -366,7 +366,46 @@ int launch_fused(const Plan &plan, const void *X, const void *Wg, const void *Wu
     }
 }
 
-// Stream-ordered scratch for the entry points that allocate.
+// Zero n 32-bit words.  A kernel rather than a memset, so that a captured
+// call holds kernels only.
+__global__ void zero_words_kernel(uint32_t *p, uint32_t n)
+{
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
+        p[i] = 0u;
+}
+
+int clear_words(uint32_t *p, int words, hipStream_t st)
+{
+    if (words <= 0)
+        return GMLP_OK;
+    hipLaunchKernelGGL(zero_words_kernel, dim3((unsigned)std::min(64, (words + 255) / 256)), dim3(256), 0, st, p,
+                       (uint32_t)words);
+    return hip_check(hipGetLastError(), "counter clear launch");
+}
+
+// A call on a workspace that was not initialised (GMLP_FRESH_WORKSPACE)
+// clears the arrival counters its steps use, if any: at most 64 KB of the
+// 128 KB counter block, which the kernels of these paths touch nothing else
+// of, and no launch at all where no step splits K.
+int clear_counters(bool fresh, int words, uint8_t *ws, const Layout &l, hipStream_t st)
+{
+    return fresh ? clear_words(reinterpret_cast<uint32_t *>(ws + l.counters_off), words, st) : GMLP_OK;
+}
+
+// Takes GMLP_FRESH_WORKSPACE out of `path`.  The fused paths' ready words
+// and give-up count need a prepared workspace, so with them the flag stays in
+// and the path is refused as unknown.
+constexpr int kFreshAuto = GMLP_PATH_AUTO | GMLP_FRESH_WORKSPACE;
+bool take_fresh(int *path)
+{
+    const int base = *path & ~GMLP_FRESH_WORKSPACE;
+    if (base == *path || (base != GMLP_PATH_AUTO && base != GMLP_PATH_GEMV && base != GMLP_PATH_MFMA))
+        return false;
+    *path = base;
+    return true;
+}
+
+// Stream-ordered scratch for the entry points that allocate; not initialised.
 struct Scratch {
     void *ptr = nullptr;
     hipStream_t stream = nullptr;
@@ -375,7 +414,7 @@ struct Scratch {
         if (ptr)
             (void)hipFreeAsync(ptr, stream);
     }
-    int alloc(size_t bytes, const Layout &l, hipStream_t st)
+    int alloc(size_t bytes, hipStream_t st)
     {
         stream = st;
         int rc = hip_check(hipMallocAsync(&ptr, bytes, st), "hipMallocAsync(workspace)");
@@ -383,7 +422,7 @@ struct Scratch {
             ptr = nullptr;
             return rc == GMLP_ERR_HIP ? fail(GMLP_ERR_NO_MEMORY, "%s", g_err) : rc;
         }
-        return hip_check(hipMemsetAsync(ptr, 0, l.h_off, st), "hipMemsetAsync(counters)");
+        return GMLP_OK;
     }
 };
 
@@ -493,6 +532,7 @@ int gmlp_forward_variant(const void *X, const void *Wg, const void *Wu, const vo
 {
     int rc;
     Variant v;
+    const bool fresh = take_fresh(&path);
     if ((rc = validate(T, D, F, X, Wg, Wu, Wd, Y)) || (rc = check_path(path, T)) ||
         (rc = check_variant(activation, beta, rmsnorm, eps, &v)))
         return rc;
@@ -514,7 +554,8 @@ int gmlp_forward_variant(const void *X, const void *Wg, const void *Wu, const vo
         return rc ? rc : ok();
     }
     void *H = ws + l.h_off;
-    if ((rc = run_gate_up_plan(plan, X, Wg, Wu, H, D, F, ws, l, v, st)) ||
+    if ((rc = clear_counters(fresh, plan_counters(plan), ws, l, st)) ||
+        (rc = run_gate_up_plan(plan, X, Wg, Wu, H, D, F, ws, l, v, st)) ||
         (rc = run_down(plan.down, H, Wd, Y, ws, l, st)))
         return rc;
     return ok();
@@ -543,9 +584,9 @@ int gmlp_forward(const void *X, const void *Wg, const void *Wu, const void *Wd, 
         return ok();
     const Layout l = make_layout(T, D, F);
     Scratch s;
-    if ((rc = s.alloc(l.total, l, static_cast<hipStream_t>(stream))))
+    if ((rc = s.alloc(l.total, static_cast<hipStream_t>(stream))))
         return rc;
-    return gmlp_forward_ex(X, Wg, Wu, Wd, Y, T, D, F, GMLP_PATH_AUTO, s.ptr, l.total, stream);
+    return gmlp_forward_ex(X, Wg, Wu, Wd, Y, T, D, F, kFreshAuto, s.ptr, l.total, stream);
 }
 
 } // extern "C"
@@ -559,13 +600,6 @@ int gmlp_forward(const void *X, const void *Wg, const void *Wu, const void *Wd, 
 static __device__ __align__(256) uint8_t scratch[GMLP_NOALLOC_SCRATCH_BYTES];
 
 namespace {
-
-// Zero n 32-bit words (the counter block of the scratch array at set-up).
-__global__ void zero_words_kernel(uint32_t *p, uint32_t n)
-{
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
-        p[i] = 0u;
-}
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
@@ -589,9 +623,7 @@ int noalloc_scratch(hipStream_t st, uint8_t **out)
         void *p = nullptr;
         if ((rc = hip_check(hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)), "hipGetSymbolAddress(scratch)")))
             return rc;
-        const uint32_t words = (uint32_t)(kCounterBytes / sizeof(uint32_t));
-        hipLaunchKernelGGL(zero_words_kernel, dim3(64), dim3(256), 0, st, static_cast<uint32_t *>(p), words);
-        if ((rc = hip_check(hipGetLastError(), "scratch counter clear launch")))
+        if ((rc = clear_words(static_cast<uint32_t *>(p), (int)(kCounterBytes / sizeof(uint32_t)), st)))
             return rc;
         g_scratch_ptr[dev] = static_cast<uint8_t *>(p);
     }
@@ -631,6 +663,7 @@ int gmlp_gate_up_variant(const void *X, const void *Wg, const void *Wu, void *H,
 {
     int rc;
     Variant v;
+    const bool fresh = take_fresh(&path);
     if ((rc = check_gate_up_args(X, Wg, Wu, H, T, D, F)) || (rc = check_single_step_path(path, T)) ||
         (rc = check_variant(activation, beta, rmsnorm, eps, &v)))
         return rc;
@@ -640,8 +673,10 @@ int gmlp_gate_up_variant(const void *X, const void *Wg, const void *Wu, void *H,
     if ((rc = check_workspace(workspace, ws_bytes, l)))
         return rc;
     const Plan plan = make_plan(T, D, F, path);
-    if ((rc = run_gate_up_plan(plan, X, Wg, Wu, H, D, F, static_cast<uint8_t *>(workspace), l, v,
-                               static_cast<hipStream_t>(stream))))
+    uint8_t *ws = static_cast<uint8_t *>(workspace);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if ((rc = clear_counters(fresh, std::max(plan.gate_up.counters, plan.gate_up_rest.counters), ws, l, st)) ||
+        (rc = run_gate_up_plan(plan, X, Wg, Wu, H, D, F, ws, l, v, st)))
         return rc;
     return ok();
 }
@@ -657,6 +692,7 @@ int gmlp_down_ws(const void *H, const void *Wd, void *Y, int64_t T, int64_t F, i
                  void *workspace, size_t ws_bytes, void *stream)
 {
     int rc;
+    const bool fresh = take_fresh(&path);
     if ((rc = check_down_args(H, Wd, Y, T, F, D)) || (rc = check_single_step_path(path, T)))
         return rc;
     if (T == 0)
@@ -665,8 +701,10 @@ int gmlp_down_ws(const void *H, const void *Wd, void *Y, int64_t T, int64_t F, i
     if ((rc = check_workspace(workspace, ws_bytes, l)))
         return rc;
     const Plan plan = make_plan(T, D, F, path);
-    if ((rc = run_down(plan.down, H, Wd, Y, static_cast<uint8_t *>(workspace), l,
-                       static_cast<hipStream_t>(stream))))
+    uint8_t *ws = static_cast<uint8_t *>(workspace);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if ((rc = clear_counters(fresh, plan.down.counters, ws, l, st)) ||
+        (rc = run_down(plan.down, H, Wd, Y, ws, l, st)))
         return rc;
     return ok();
 }
@@ -681,9 +719,9 @@ int gmlp_gate_up(const void *X, const void *Wg, const void *Wu, void *H, int64_t
         return ok();
     const Layout l = make_layout(T, D, F);
     Scratch s;
-    if ((rc = s.alloc(l.total, l, static_cast<hipStream_t>(stream))))
+    if ((rc = s.alloc(l.total, static_cast<hipStream_t>(stream))))
         return rc;
-    return gmlp_gate_up_ws(X, Wg, Wu, H, T, D, F, GMLP_PATH_AUTO, s.ptr, l.total, stream);
+    return gmlp_gate_up_ws(X, Wg, Wu, H, T, D, F, kFreshAuto, s.ptr, l.total, stream);
 }
 
 int gmlp_down(const void *H, const void *Wd, void *Y, int64_t T, int64_t F, int64_t D, void *stream)
@@ -695,9 +733,9 @@ int gmlp_down(const void *H, const void *Wd, void *Y, int64_t T, int64_t F, int6
         return ok();
     const Layout l = make_layout(T, D, F);
     Scratch s;
-    if ((rc = s.alloc(l.total, l, static_cast<hipStream_t>(stream))))
+    if ((rc = s.alloc(l.total, static_cast<hipStream_t>(stream))))
         return rc;
-    return gmlp_down_ws(H, Wd, Y, T, F, D, GMLP_PATH_AUTO, s.ptr, l.total, stream);
+    return gmlp_down_ws(H, Wd, Y, T, F, D, kFreshAuto, s.ptr, l.total, stream);
 }
 
 } // extern "C"
@@ -710,19 +748,21 @@ int gmlp_down(const void *H, const void *Wd, void *Y, int64_t T, int64_t F, int6
 
 namespace {
 
-int launch_softmax_rows(const void *X, uint16_t *P, float *sums, int64_t M, int64_t K, hipStream_t st)
+int launch_softmax_rows(const void *X, uint16_t *P, float *sums, int64_t M, int64_t K, uint32_t *counters, int words,
+                        hipStream_t st)
 {
     const dim3 grid((unsigned)cdiv(M, kSoftmaxThreads / 64)), block(kSoftmaxThreads);
     const uint16_t *x = static_cast<const uint16_t *>(X);
+    const auto launch = [&](auto r) {
+        hipLaunchKernelGGL(softmax_exp_rows_kernel<decltype(r)::value>, grid, block, 0, st, x, P, sums, (int)M, (int)K,
+                           counters, words);
+    };
     switch (softmax_chunks_per_lane((int)K)) {
-    case 1: hipLaunchKernelGGL(softmax_exp_rows_kernel<1>, grid, block, 0, st, x, P, sums, (int)M, (int)K); break;
-    case 2: hipLaunchKernelGGL(softmax_exp_rows_kernel<2>, grid, block, 0, st, x, P, sums, (int)M, (int)K); break;
-    case 4: hipLaunchKernelGGL(softmax_exp_rows_kernel<4>, grid, block, 0, st, x, P, sums, (int)M, (int)K); break;
-    case 8: hipLaunchKernelGGL(softmax_exp_rows_kernel<8>, grid, block, 0, st, x, P, sums, (int)M, (int)K); break;
-    default:
-        hipLaunchKernelGGL(softmax_exp_rows_kernel<kSoftmaxMaxChunks>, grid, block, 0, st, x, P, sums, (int)M,
-                           (int)K);
-        break;
+    case 1: launch(std::integral_constant<int, 1>{}); break;
+    case 2: launch(std::integral_constant<int, 2>{}); break;
+    case 4: launch(std::integral_constant<int, 4>{}); break;
+    case 8: launch(std::integral_constant<int, 8>{}); break;
+    default: launch(std::integral_constant<int, kSoftmaxMaxChunks>{}); break;
     }
     return hip_check(hipGetLastError(), "softmax exp/row-sum launch");
 }
@@ -761,6 +801,7 @@ int softmax_matmul_ws(const void *X, const void *Y, void *Z, int64_t M, int64_t 
                       void *workspace, size_t ws_bytes, void *stream)
 {
     int rc;
+    const bool fresh = take_fresh(&path);
     if ((rc = check_smm_args(X, Y, Z, M, K, N)) || (rc = check_single_step_path(path, M)))
         return rc;
     if (M == 0)
@@ -775,7 +816,10 @@ int softmax_matmul_ws(const void *X, const void *Y, void *Z, int64_t M, int64_t 
     uint16_t *P = reinterpret_cast<uint16_t *>(ws + l.h_off);
     float *sums = reinterpret_cast<float *>(ws + l.rrms_off);
     const Step s = smm_matmul_step(M, K, N, path);
-    if ((rc = launch_softmax_rows(X, P, sums, M, K, st)) || (rc = run_down(s, P, Y, Z, ws, l, st, sums)))
+    // The first kernel clears the matmul's counters on a fresh workspace.
+    if ((rc = launch_softmax_rows(X, P, sums, M, K, reinterpret_cast<uint32_t *>(ws + l.counters_off),
+                                  fresh ? s.counters : 0, st)) ||
+        (rc = run_down(s, P, Y, Z, ws, l, st, sums)))
         return rc;
     return ok();
 }
@@ -794,7 +838,7 @@ int softmax_matmul_exp_rows(const void *X, void *P, float *s, int64_t M, int64_t
         return fail(GMLP_ERR_INVALID_ARG, "X, P and s must not overlap");
     if (M == 0)
         return ok();
-    if ((rc = launch_softmax_rows(X, static_cast<uint16_t *>(P), s, M, K, static_cast<hipStream_t>(stream))))
+    if ((rc = launch_softmax_rows(X, static_cast<uint16_t *>(P), s, M, K, nullptr, 0, static_cast<hipStream_t>(stream))))
         return rc;
     return ok();
 }
@@ -833,9 +877,9 @@ int softmax_matmul(const void *X, const void *Y, void *Z, int64_t M, int64_t K, 
         return ok();
     const Layout l = smm_layout(M, K, N);
     Scratch s;
-    if ((rc = s.alloc(l.total, l, static_cast<hipStream_t>(stream))))
+    if ((rc = s.alloc(l.total, static_cast<hipStream_t>(stream))))
         return rc;
-    return softmax_matmul_ws(X, Y, Z, M, K, N, GMLP_PATH_AUTO, s.ptr, l.total, stream);
+    return softmax_matmul_ws(X, Y, Z, M, K, N, kFreshAuto, s.ptr, l.total, stream);
 }
 
 } // extern "C"

@@ -191,6 +191,13 @@ struct Plan {
 };
 
 
+// Arrival counters the steps of a two-kernel plan use, from the start of the
+// counter block.
+int plan_counters(const Plan &p)
+{
+    return std::max({p.gate_up.counters, p.gate_up_rest.counters, p.down.counters});
+}
+
 struct Layout {
     size_t counters_off = 0, h_off = 0, partial_off = 0, rrms_off = 0, total = 0;
     int counters = 0; // most arrival counters any path uses for this shape

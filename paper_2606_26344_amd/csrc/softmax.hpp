@@ -101,8 +101,13 @@ __device__ __forceinline__ float chunks_exp(const u32x4 (&v)[R], uint16_t *p, in
 // both cases, so s does not depend on which case ran.
 template <int R>
 __global__ __launch_bounds__(kSoftmaxThreads) void softmax_exp_rows_kernel(const uint16_t *X, uint16_t *P,
-                                                                           float *s, int M, int K)
+                                                                           float *s, int M, int K,
+                                                                           uint32_t *counters, int words)
 {
+    // Clears the arrival counters of the matmul that follows, where asked to
+    // (a launch of its own for that took 2-4 us of a 55 us call).
+    for (int c = blockIdx.x * kSoftmaxThreads + threadIdx.x; c < words; c += gridDim.x * kSoftmaxThreads)
+        counters[c] = 0u;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int i = blockIdx.x * (kSoftmaxThreads / 64) + wave;
     if (i >= M)

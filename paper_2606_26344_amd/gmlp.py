@@ -6,9 +6,12 @@ Argument marshalling only: every step of the Gated MLP runs in the library's
 HIP kernels.  PyTorch supplies device memory and the current HIP stream.  The
 names mirror the C entry points:
 
-    forward(x, wg, wu, wd)   -> gmlp_forward / gmlp_forward_ex / gmlp_forward_variant
-    gate_up(x, wg, wu)       -> gmlp_gate_up / gmlp_gate_up_ws / gmlp_gate_up_variant
-    down(h, wd)              -> gmlp_down / gmlp_down_ws
+    forward(x, wg, wu, wd)   -> gmlp_forward_ex / gmlp_forward_variant
+    gate_up(x, wg, wu)       -> gmlp_gate_up_ws / gmlp_gate_up_variant
+    down(h, wd)              -> gmlp_down_ws
+
+Without a workspace they take memory for one call from torch's caching
+allocator on the call's stream (and mark it GMLP_FRESH_WORKSPACE).
 
 forward() and gate_up() also take the members of the Gated MLP family:
 activation "silu" (default), "swish" (g * sigmoid(beta g)) or "sigmoid"
@@ -35,6 +38,8 @@ HEADERS = [HEADER, os.path.join(os.path.dirname(HERE), "include", "softmax_matmu
 PATH_AUTO, PATH_GEMV, PATH_MFMA, PATH_FUSED, PATH_FUSED_MFMA = 0, 1, 2, 3, 4
 _PATHS = {"auto": PATH_AUTO, "gemv": PATH_GEMV, "mfma": PATH_MFMA, "fused": PATH_FUSED,
           "fused_mfma": PATH_FUSED_MFMA}
+FRESH_WORKSPACE = 256  # or'ed into a path: the workspace has not been prepared
+ERR_NO_MEMORY = 4
 ACT_SILU, ACT_SWISH, ACT_SIGMOID = 0, 1, 2
 ACTIVATIONS = {"silu": ACT_SILU, "swish": ACT_SWISH, "sigmoid": ACT_SIGMOID}
 
@@ -128,13 +133,11 @@ def _check(rc: int) -> None:
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
-def _stream(stream) -> ctypes.c_void_p:
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+def _stream(stream) -> int:
+    return (torch.cuda.current_stream() if stream is None else stream).cuda_stream
 
 
 def _empty(shape, dtype, device, stream=None) -> torch.Tensor:
@@ -150,7 +153,34 @@ def _empty(shape, dtype, device, stream=None) -> torch.Tensor:
         return torch.empty(shape, dtype=dtype, device=device)
 
 
+def _scratch(nbytes: int, rows: int, device, stream, plain: bool, invalid: str):
+    """Memory for one call's workspace from torch's caching allocator, as
+    (tensor to keep until the call is enqueued, 256-byte aligned address);
+    (None, None) where the call takes none (no rows, or a shape that the
+    library refuses).  Its contents are undefined: the call is made with
+    FRESH_WORKSPACE.  hipMallocAsync in the library costs 9 us of host time a
+    call and, since its pool gives its memory back whenever the device is
+    synchronised, 30 to 40 us more on the first call after that.  ``plain``
+    calls (those of the C entry points that allocate) report a refused shape
+    and exhausted memory as those do; the others raise ``invalid`` and torch's
+    own error."""
+    if not nbytes and not plain:
+        raise ValueError(invalid)
+    if not nbytes or not rows:
+        return None, None
+    try:
+        t = _empty((nbytes + 256,), torch.uint8, device, stream)
+    except torch.OutOfMemoryError as e:
+        if not plain:
+            raise
+        raise GmlpError(ERR_NO_MEMORY, "workspace of %d bytes: %s" % (nbytes, e)) from e
+    return t, (t.data_ptr() + 255) & ~255
+
+
 def _expect(t: torch.Tensor, name: str, shape, device) -> None:
+    if (isinstance(t, torch.Tensor) and t.dtype is torch.bfloat16 and t.is_cuda and t.device == device
+            and t.shape == shape and t.is_contiguous()):
+        return
     if not isinstance(t, torch.Tensor):
         raise TypeError("%s must be a torch.Tensor" % name)
     if t.dtype != torch.bfloat16:
@@ -241,22 +271,29 @@ def forward(x: torch.Tensor, wg: torch.Tensor, wu: torch.Tensor, wd: torch.Tenso
     _expect(wd, "wd", (F, D), dev)
     if out is None:
         out = _empty((T, D), torch.bfloat16, dev, stream)
-    _expect(out, "out", (T, D), dev)
-    lib = library()
-    st = _stream(stream)
-    plain = activation == "silu" and not rmsnorm
-    if workspace is None and path == "auto" and plain:
-        _check(lib.gmlp_forward(_ptr(x), _ptr(wg), _ptr(wu), _ptr(wd), _ptr(out), T, D, F, st))
-        return out
-    if workspace is None:
-        workspace = Workspace(T, D, F, device=dev, stream=stream)
-    if plain:
-        _check(lib.gmlp_forward_ex(_ptr(x), _ptr(wg), _ptr(wu), _ptr(wd), _ptr(out), T, D, F,
-                                   _PATHS[path], _ptr(workspace.buffer), workspace.nbytes, st))
     else:
-        _check(lib.gmlp_forward_variant(_ptr(x), _ptr(wg), _ptr(wu), _ptr(wd), _ptr(out), T, D, F,
-                                        *_variant(activation, beta, rmsnorm, eps), _PATHS[path],
-                                        _ptr(workspace.buffer), workspace.nbytes, st))
+        _expect(out, "out", (T, D), dev)
+    lib = library()
+    variant = None
+    if activation != "silu" or rmsnorm:
+        variant = _variant(activation, beta, rmsnorm, eps)
+    code = _PATHS[path]
+    if workspace is None and code in (PATH_FUSED, PATH_FUSED_MFMA):
+        workspace = Workspace(T, D, F, device=dev, stream=stream)
+    st = _stream(stream)
+    if workspace is None:
+        nbytes = workspace_size(T, D, F)
+        keep, ws = _scratch(nbytes, T, dev, stream, variant is None and code == PATH_AUTO,
+                            "invalid shape T=%d D=%d F=%d" % (T, D, F))
+        code |= FRESH_WORKSPACE
+    else:
+        keep, ws, nbytes = None, workspace.buffer.data_ptr(), workspace.nbytes
+    if variant is None:
+        _check(lib.gmlp_forward_ex(x.data_ptr(), wg.data_ptr(), wu.data_ptr(), wd.data_ptr(), out.data_ptr(), T, D, F,
+                                   code, ws, nbytes, st))
+    else:
+        _check(lib.gmlp_forward_variant(x.data_ptr(), wg.data_ptr(), wu.data_ptr(), wd.data_ptr(), out.data_ptr(), T,
+                                        D, F, *variant, code, ws, nbytes, st))
     return out
 
 
@@ -289,23 +326,25 @@ def gate_up(x: torch.Tensor, wg: torch.Tensor, wu: torch.Tensor,
     _expect(wu, "wu", (D, F), dev)
     if out is None:
         out = _empty((T, F), torch.bfloat16, dev, stream)
-    _expect(out, "out", (T, F), dev)
-    plain = activation == "silu" and not rmsnorm
-    if workspace is None and path == "auto" and plain:
-        _check(library().gmlp_gate_up(_ptr(x), _ptr(wg), _ptr(wu), _ptr(out), T, D, F,
-                                      _stream(stream)))
-        return out
-    if workspace is None:
-        workspace = Workspace(T, D, F, device=dev, stream=stream)
-    if plain:
-        _check(library().gmlp_gate_up_ws(_ptr(x), _ptr(wg), _ptr(wu), _ptr(out), T, D, F,
-                                         _PATHS[path], _ptr(workspace.buffer), workspace.nbytes,
-                                         _stream(stream)))
     else:
-        _check(library().gmlp_gate_up_variant(_ptr(x), _ptr(wg), _ptr(wu), _ptr(out), T, D, F,
-                                              *_variant(activation, beta, rmsnorm, eps),
-                                              _PATHS[path], _ptr(workspace.buffer),
-                                              workspace.nbytes, _stream(stream)))
+        _expect(out, "out", (T, F), dev)
+    plain = activation == "silu" and not rmsnorm
+    code = _PATHS[path]
+    st = _stream(stream)
+    if workspace is None:
+        nbytes = workspace_size(T, D, F)
+        keep, ws = _scratch(nbytes, T, dev, stream, plain and code == PATH_AUTO,
+                            "invalid shape T=%d D=%d F=%d" % (T, D, F))
+        if code not in (PATH_FUSED, PATH_FUSED_MFMA):  # refused by the library
+            code |= FRESH_WORKSPACE
+    else:
+        keep, ws, nbytes = None, workspace.buffer.data_ptr(), workspace.nbytes
+    if plain:
+        _check(library().gmlp_gate_up_ws(x.data_ptr(), wg.data_ptr(), wu.data_ptr(), out.data_ptr(), T, D, F, code, ws,
+                                         nbytes, st))
+    else:
+        _check(library().gmlp_gate_up_variant(x.data_ptr(), wg.data_ptr(), wu.data_ptr(), out.data_ptr(), T, D, F,
+                                              *_variant(activation, beta, rmsnorm, eps), code, ws, nbytes, st))
     return out
 
 
@@ -319,14 +358,18 @@ def down(h: torch.Tensor, wd: torch.Tensor, out: Optional[torch.Tensor] = None,
     _expect(wd, "wd", (F, D), dev)
     if out is None:
         out = _empty((T, D), torch.bfloat16, dev, stream)
-    _expect(out, "out", (T, D), dev)
-    if workspace is None and path == "auto":
-        _check(library().gmlp_down(_ptr(h), _ptr(wd), _ptr(out), T, F, D, _stream(stream)))
-        return out
+    else:
+        _expect(out, "out", (T, D), dev)
+    code = _PATHS[path]
+    st = _stream(stream)
     if workspace is None:
-        workspace = Workspace(T, D, F, device=dev, stream=stream)
-    _check(library().gmlp_down_ws(_ptr(h), _ptr(wd), _ptr(out), T, F, D, _PATHS[path],
-                                  _ptr(workspace.buffer), workspace.nbytes, _stream(stream)))
+        nbytes = workspace_size(T, D, F)
+        keep, ws = _scratch(nbytes, T, dev, stream, code == PATH_AUTO, "invalid shape T=%d D=%d F=%d" % (T, D, F))
+        if code not in (PATH_FUSED, PATH_FUSED_MFMA):  # refused by the library
+            code |= FRESH_WORKSPACE
+    else:
+        keep, ws, nbytes = None, workspace.buffer.data_ptr(), workspace.nbytes
+    _check(library().gmlp_down_ws(h.data_ptr(), wd.data_ptr(), out.data_ptr(), T, F, D, code, ws, nbytes, st))
     return out
 
 

@@ -4,7 +4,7 @@
 Argument marshalling only: the exponentials, row sums, matmul and divide run
 in the library's HIP kernels.  Names mirror the C entry points:
 
-    softmax_matmul(x, y)    -> softmax_matmul / softmax_matmul_ws
+    softmax_matmul(x, y)    -> softmax_matmul_ws
     exp_rows(x)             -> softmax_matmul_exp_rows   (P = exp(x - rowmax), s)
     divide(p, s, y)         -> softmax_matmul_divide_ws  ((p y) / s, row by row)
     describe(M, K, N)       -> softmax_matmul_describe
@@ -20,7 +20,8 @@ from typing import Optional
 
 import torch
 
-from .gmlp import _PATHS, Workspace, _check, _empty, _expect, _parse_plan, _ptr, _stream, library
+from .gmlp import (FRESH_WORKSPACE, PATH_AUTO, PATH_FUSED, PATH_FUSED_MFMA, _PATHS, Workspace, _check, _empty,
+                   _expect, _parse_plan, _ptr, _scratch, _stream, library)
 
 
 def workspace_size(M: int, K: int, N: int) -> int:
@@ -55,15 +56,18 @@ def softmax_matmul(x: torch.Tensor, y: torch.Tensor, out: Optional[torch.Tensor]
     _expect(y, "y", (K, N), dev)
     if out is None:
         out = _empty((M, N), torch.bfloat16, dev, stream)
-    _expect(out, "out", (M, N), dev)
+    else:
+        _expect(out, "out", (M, N), dev)
+    code = _PATHS[path]
     st = _stream(stream)
-    if workspace is None and path == "auto":
-        _check(library().softmax_matmul(_ptr(x), _ptr(y), _ptr(out), M, K, N, st))
-        return out
     if workspace is None:
-        workspace = make_workspace(M, K, N, device=dev, stream=stream)
-    _check(library().softmax_matmul_ws(_ptr(x), _ptr(y), _ptr(out), M, K, N, _PATHS[path],
-                                       _ptr(workspace.buffer), workspace.nbytes, st))
+        nbytes = workspace_size(M, K, N)
+        keep, ws = _scratch(nbytes, M, dev, stream, code == PATH_AUTO, "invalid shape M=%d K=%d N=%d" % (M, K, N))
+        if code not in (PATH_FUSED, PATH_FUSED_MFMA):  # refused by the library
+            code |= FRESH_WORKSPACE
+    else:
+        keep, ws, nbytes = None, workspace.buffer.data_ptr(), workspace.nbytes
+    _check(library().softmax_matmul_ws(x.data_ptr(), y.data_ptr(), out.data_ptr(), M, K, N, code, ws, nbytes, st))
     return out
 
 
