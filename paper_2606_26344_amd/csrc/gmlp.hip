@@ -159,8 +159,7 @@ int launch_row_rms(const Step &s, const void *X, uint8_t *ws, const Layout &l, c
                    hipStream_t st, const float **rrms)
 {
     float *r = reinterpret_cast<float *>(ws + l.rrms_off);
-    const int per = kRowRmsThreads / 64;
-    hipLaunchKernelGGL(row_rms_kernel, dim3((unsigned)cdiv(s.N, per)), dim3(kRowRmsThreads), 0, st,
+    hipLaunchKernelGGL(row_rms_kernel, dim3((unsigned)std::min(s.N, kRowRmsBlocks)), dim3(kRowRmsThreads), 0, st,
                        static_cast<const uint16_t *>(X), r, s.N, s.K, v.eps);
     *rrms = r;
     return hip_check(hipGetLastError(), "row RMS launch");
