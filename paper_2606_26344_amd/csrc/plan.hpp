@@ -164,7 +164,7 @@ struct Step {
     // both run as one split-K launch, the whole tiles' blocks first.
     int tile_base = 0, tile_count = 0;
     int tail_tiles = 0, tail_splits = 1, tail_k_split = 0;
-    int64_t block_macs = 0; // GEMM: multiply-adds of one block of the main launch
+    int64_t block_macs = 0; // GEMM: multiply-adds of one block of the main launch, at the splits that fill a round
 };
 
 // The split part of a step with a tail: its last tail_tiles tiles, split
@@ -237,6 +237,38 @@ void choose_splits(Step &s, int tiles, int target, int tile_k, int min_tiles)
     s.splits = (int)cdiv(s.K, s.k_split);
 }
 
+// Splits of K above 128 tokens: the count up to that of choose_splits with the
+// least estimated time.  A k-tile takes its staged bytes at 50 GB/s per CU (what
+// the ring kernels reach: 0.66 us for the 128 x 128 down tiles, 0.98 for the
+// gate/up ones), an exchange 4 us, the partial tile of each split read by the
+// last block at 54 GB/s, and all blocks' partial tiles written at 8 TB/s.
+// Splitting to fill the chip whatever K is, as few as two k-tiles per split,
+// spent most of a small step in the exchange.  Measured, before and after, us:
+// down T = 328, D = 880, F = 2296 20.1 -> 15.4 (12 splits to 4); the whole MLP
+// T = 140, D = 1024, F = 4096 88.6 -> 41.2, T = 3839, D = 256, F = 512 39.8 -> 22.7,
+// T = 1505, D = 256, F = 512 25.6 -> 17.7.  Where K is long the count stays (T = 222,
+// D = 4096, F = 16384: 4 splits of the down step).  The 256-column down tiles,
+// which are chosen by the length of their splits, keep the other rule.
+void choose_splits_by_time(Step &s, int tiles, int target, int tile_k, size_t stage_bytes, size_t tile_bytes)
+{
+    const int64_t ktiles = cdiv(s.K, tile_k);
+    const int64_t most = tiles < target ? std::min<int64_t>(target / tiles, std::max<int64_t>(1, ktiles / 2)) : 1;
+    double best = 0.0;
+    int64_t per = ktiles;
+    for (int64_t n = 1; n <= most; ++n) {
+        const int64_t p = cdiv(ktiles, n), used = cdiv(ktiles, p);
+        double t = (double)p * (double)stage_bytes / 50e3; // us
+        if (used > 1)
+            t += 4.0 + (double)used * (double)tile_bytes / 54e3 + (double)(used * tiles) * (double)tile_bytes / 8e6;
+        if (n == 1 || t < best) {
+            best = t;
+            per = p;
+        }
+    }
+    s.k_split = (int)(per * tile_k);
+    s.splits = (int)cdiv(s.K, s.k_split);
+}
+
 template <class S>
 void gemm_step(Step &s, Kind kind, int M, int N, int K, int nw, bool allow_split, int group_m,
                int min_k_tiles = 2)
@@ -253,9 +285,16 @@ void gemm_step(Step &s, Kind kind, int M, int N, int K, int nw, bool allow_split
     s.tail_tiles = 0;
     s.tail_splits = 1;
     s.tail_k_split = 0;
-    if (allow_split)
+    int reserve = 1; // splits the workspace holds partial sums for
+    int macs_rows = K;
+    if (allow_split) {
         choose_splits(s, tiles, kBlockTarget, S::BK, min_k_tiles);
-    else {
+        reserve = s.splits;
+        macs_rows = s.k_split;
+        if (N > 128 && kind != K_GEMM_DN_L && kind != K_GEMM_DN_X)
+            choose_splits_by_time(s, tiles, kBlockTarget, S::BK, (size_t)(S::BMW * nw + S::BN) * S::BK * 2,
+                                  (size_t)S::BMW * S::BN * nw * sizeof(float));
+    } else {
         s.splits = 1;
         s.k_split = K;
         const int rem = tiles % kBlockTarget;
@@ -273,13 +312,15 @@ void gemm_step(Step &s, Kind kind, int M, int N, int K, int nw, bool allow_split
         }
     }
     s.blocks = s.tile_count * s.splits;
-    s.block_macs = (int64_t)S::BMW * S::BN * nw * s.k_split;
+    s.block_macs = (int64_t)S::BMW * S::BN * nw * macs_rows;
     s.threads = S::NTHREADS;
     s.counters = std::max(s.splits > 1 ? tiles : 0, s.tail_tiles);
     // Partial sums of whole tiles (padded), [split][tile][wave][piece][lane];
     // the tail tiles use the space of a split step's partial sums.
     const size_t tile_bytes = (size_t)S::BMW * S::BN * nw * sizeof(float);
-    s.partial_bytes = std::max(s.splits > 1 ? (size_t)s.splits * tiles * tile_bytes : 0,
+    // Space for `reserve` splits (which covers fewer), so that the workspace of a
+    // shape, and which other shapes it serves, does not depend on the estimate.
+    s.partial_bytes = std::max(reserve > 1 ? (size_t)reserve * tiles * tile_bytes : 0,
                                (size_t)s.tail_splits * s.tail_tiles * tile_bytes);
 }
 
