@@ -176,6 +176,8 @@ int run_gate_up(const Step &s, const void *X, const void *Wg, const void *Wu, vo
     }
     switch (s.kind) {
     case K_GEMM_GU_L: {
+        if (!s.tail_tiles && stream_weights(s))
+            return launch_gemm<GateUpLarge, EPI_GATE_MUL, false, true>(s, Wg, Wu, X, H, ws, l, v, rrms, nullptr, st);
         if (!s.tail_tiles)
             return launch_gemm<GateUpLarge, EPI_GATE_MUL, false>(s, Wg, Wu, X, H, ws, l, v, rrms, nullptr, st);
         return launch_gemm<GateUpLarge, EPI_GATE_MUL, true>(tail_step(s), Wg, Wu, X, H, ws, l, v, rrms, nullptr, st,
@@ -190,7 +192,10 @@ int run_gate_up(const Step &s, const void *X, const void *Wg, const void *Wu, vo
         return stream_weights(s) ? launch_gemm<GateUpMid, EPI_GATE_MUL, true, true>(s, Wg, Wu, X, H, ws, l, v, rrms, nullptr, st)
                                  : launch_gemm<GateUpMid, EPI_GATE_MUL, true, false>(s, Wg, Wu, X, H, ws, l, v, rrms, nullptr, st);
     case K_GEMM_GU_Y:
-        return launch_gemm<GateUp192, EPI_GATE_MUL, false>(s, Wg, Wu, X, H, ws, l, v, rrms, nullptr, st);
+        if (s.tail_tiles)
+            return fail(GMLP_ERR_INVALID_ARG, "internal: 192-token gate/up tiles with a tail");
+        return stream_weights(s) ? launch_gemm<GateUp192, EPI_GATE_MUL, false, true>(s, Wg, Wu, X, H, ws, l, v, rrms, nullptr, st)
+                                 : launch_gemm<GateUp192, EPI_GATE_MUL, false, false>(s, Wg, Wu, X, H, ws, l, v, rrms, nullptr, st);
     case K_GEMM_GU_W: // one token tile: always streamed
         return launch_gemm<GateUpMid96, EPI_GATE_MUL, true, true>(s, Wg, Wu, X, H, ws, l, v, rrms, nullptr, st);
     case K_GEMM_GU_P: // one token tile, a G and a U block per column tile

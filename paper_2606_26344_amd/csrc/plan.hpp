@@ -546,7 +546,20 @@ Plan make_plan(int64_t T, int64_t D, int64_t F, int path)
     // tiles, gate/up: T = 257 111.8 -> 89.0 us, 320 114.2 -> 93.5, 384
     // 115.8 -> 98.3; 8 waves with 64-row k-tiles were 6-11% slower).
     const int64_t tiles192 = cdiv(T, GateUp192::BN) * cdiv(F, GateUp192::BMW);
-    if (T > 256 && T <= 2 * GateUp192::BN && tiles192 <= kBlockTarget && tiles192 >= kBlockTarget * 3 / 4)
+    // 129 to 256 tokens with 129 to 256 column tiles, where two 128-token
+    // tiles of each would take a second round: one 192- or 256-token tile
+    // instead, in one round, each weight element read once (the weights
+    // streamed).  Measured, gate/up: D = 8192, F = 28672 T = 129 311.8 -> 199.0 us,
+    // 192 308.9 -> 198.6, 256 318.0 -> 240.6; D = 4400, F = 16648 (131 tiles) T = 129
+    // 135.8 -> 101.4, 193 143.8 -> 124.5; D = 4096, F = 20480 T = 160 129.9 -> 98.2,
+    // 256 139.6 -> 116.3.
+    const int64_t columns = cdiv(F, GateUpLarge::BMW);
+    const bool one_round = columns > kBlockTarget / 2 && columns <= kBlockTarget;
+    if (T > GateUpSmall::BN && T <= GateUp192::BN && one_round)
+        gemm_step<GateUp192>(p.gate_up, K_GEMM_GU_Y, (int)F, (int)T, (int)D, 2, false, kGroupGateUp);
+    else if (T > GateUp192::BN && T <= 256 && one_round)
+        gemm_step<GateUpLarge>(p.gate_up, K_GEMM_GU_L, (int)F, (int)T, (int)D, 2, false, kGroupGateUp);
+    else if (T > 256 && T <= 2 * GateUp192::BN && tiles192 <= kBlockTarget && tiles192 >= kBlockTarget * 3 / 4)
         gemm_step<GateUp192>(p.gate_up, K_GEMM_GU_Y, (int)F, (int)T, (int)D, 2, false, kGroupGateUp);
     else if (large_tiles >= 512 || (T > 256 && large_tiles >= 192))
         gemm_step<GateUpLarge>(p.gate_up, K_GEMM_GU_L, (int)F, (int)T, (int)D, 2, false, kGroupGateUp);
@@ -853,7 +866,8 @@ std::string shape_name()
 std::string kernel_name(const Step &s, bool gate_up)
 {
     switch (s.kind) {
-    case K_GEMM_GU_L: return "gemm_mfma_kernel<" + shape_name<GateUpLarge>() + ", 0, false, false>";
+    case K_GEMM_GU_L:
+        return "gemm_mfma_kernel<" + shape_name<GateUpLarge>() + ", 0, false, " + (stream_weights(s) ? "true>" : "false>");
     case K_GEMM_GU_S:
         return "gemm_mfma_kernel<" + shape_name<GateUpSmall>() + ", 0, true, " + (stream_weights(s) ? "true>" : "false>");
     case K_GEMM_DN_L:
@@ -868,7 +882,8 @@ std::string kernel_name(const Step &s, bool gate_up)
     case K_GEMM_DN_M:
         return "gemm_mfma_kernel<" + shape_name<DownMid>() + ", 1, true, " + (stream_weights(s) ? "true>" : "false>");
     case K_GEMM_GU_W: return "gemm_mfma_kernel<" + shape_name<GateUpMid96>() + ", 0, true, true>";
-    case K_GEMM_GU_Y: return "gemm_mfma_kernel<" + shape_name<GateUp192>() + ", 0, false, false>";
+    case K_GEMM_GU_Y:
+        return "gemm_mfma_kernel<" + shape_name<GateUp192>() + ", 0, false, " + (stream_weights(s) ? "true>" : "false>");
     case K_GEMM_DN_W: return "gemm_mfma_kernel<" + shape_name<DownMid96>() + ", 1, true, true>";
     case K_GEMM_DN_Q: return "gemm_mfma_kernel<" + shape_name<DownMid160>() + ", 1, true, true>";
     case K_GEMM_DN_Y:
