@@ -1,6 +1,6 @@
 """How K is split above 128 tokens: few splits where K is short, since the
-last block of a tile reads every split's fp32 partial tile.  The plans on the CPU; the kernels at those splits on the GPU, against
-the oracle."""
+last block of a tile reads every split's fp32 partial tile.  The plans on the
+CPU; the kernels at those splits on the GPU, against the oracle."""
 import numpy as np
 import pytest
 import torch
