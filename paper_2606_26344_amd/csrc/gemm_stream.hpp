@@ -239,19 +239,26 @@ __device__ __forceinline__ void stream_tile(const GemmParams &p, int block, f32x
             return;
         if (threadIdx.x == 0)
             __hip_atomic_store(p.counters + tile, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        // The other splits' pieces, C splits in flight at once (a slot
-        // past the last reloads the first, and is not added), and this
-        // block's own at its place in the order.
+        // The other splits' pieces, up to C splits in flight at once, and this
+        // block's own at its place in the order.  What does not fill a group
+        // takes smaller ones, where a slot past the last reloads the last and
+        // is not added: a whole group of spare slots costs as much as one of
+        // real ones (down step with whole groups only: D = 1032, F = 1032, T = 8,
+        // two splits and 31 spare loads a piece, 10.1 us against 7.0; D = 1024,
+        // F = 4096, T = 16, eight splits, 11.0 against 7.6).
         constexpr int C = PIECES >= 32 ? 1 : 32 / PIECES;
+        const int others = p.splits - 1;
         f32x4 tot[PIECES];
 #pragma unroll
         for (int q = 0; q < PIECES; ++q)
             tot[q] = f32x4{};
-        for (int s0 = 0; s0 < p.splits - 1; s0 += C) {
-            f32x4 x[C][PIECES];
+        int s0 = 0;
+        auto add_group = [&](auto size) __attribute__((always_inline)) {
+            constexpr int G = decltype(size)::value;
+            f32x4 x[G][PIECES];
 #pragma unroll
-            for (int u = 0; u < C; ++u) {
-                const int o = s0 + u < p.splits - 1 ? s0 + u : 0;
+            for (int u = 0; u < G; ++u) {
+                const int o = min(s0 + u, others - 1);
                 const uint32_t sb = wave_base(o + (o >= split));
 #pragma unroll
                 for (int q = 0; q < PIECES; ++q)
@@ -259,18 +266,25 @@ __device__ __forceinline__ void stream_tile(const GemmParams &p, int block, f32x
                         f32x4, __builtin_amdgcn_raw_buffer_load_b128(prs, lane_off, sb + q * 1024u, kCoherent));
             }
 #pragma unroll
-            for (int u = 0; u < C; ++u) {
-                if (s0 + u == split && split < p.splits - 1)
+            for (int u = 0; u < G; ++u) {
+                if (s0 + u == split && split < others)
 #pragma unroll
                     for (int q = 0; q < PIECES; ++q)
                         tot[q] += piece(q);
-                if (s0 + u < p.splits - 1)
+                if (s0 + u < others)
 #pragma unroll
                     for (int q = 0; q < PIECES; ++q)
                         tot[q] += x[u][q];
             }
-        }
-        if (split == p.splits - 1)
+            s0 += G;
+        };
+        while (s0 + C <= others)
+            add_group(std::integral_constant<int, C>{});
+        while (s0 + 2 < others)
+            add_group(std::integral_constant<int, (C < 8 ? C : 8)>{});
+        if (s0 < others)
+            add_group(std::integral_constant<int, (C < 2 ? C : 2)>{});
+        if (split == others)
 #pragma unroll
             for (int q = 0; q < PIECES; ++q)
                 tot[q] += piece(q);

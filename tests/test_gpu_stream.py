@@ -102,6 +102,32 @@ def test_stream_softmax_matmul(M, K, N):
     _check(_f64(z), oracle.softmax_matmul_rows(X, Y), "M=%d K=%d N=%d" % (M, K, N))
 
 
+# The last block of a tile adds the other splits in groups (32, 8 and 2 of
+# them for one token tile of a down step, fewer for more): two splits to some
+# sixty, whole groups and every kind of remainder, with one, two, four and
+# eight 16-token tiles.
+@pytest.mark.parametrize("K", [1032, 1544, 2056, 3080, 5128, 9224, 17416, 33800])
+@pytest.mark.parametrize("T", [8, 24, 64, 128])
+def test_stream_split_exchange(orc, T, K):
+    N = 72
+    down, gate_up = gmlp.describe(T, N, K)[1], gmlp.describe(T, K, N)[0]
+    assert _is_stream(down) and _is_stream(gate_up) and down[3] > 1 and gate_up[3] > 1, (down, gate_up)
+    print("T=%d K=%d splits: down %d, gate/up %d" % (T, K, down[3], gate_up[3]), flush=True)
+    ws, ws2 = gmlp.Workspace(T, N, K), gmlp.Workspace(T, K, N)
+    rng = np.random.default_rng(T + K)
+    H, Wd = (I.f32_to_bf16_bits(rng.standard_normal(s).astype(np.float32) * a)
+             for s, a in (((T, K), 1.0), ((K, N), K ** -0.5)))
+    y = [gmlp.down(gmlp.from_bf16_bits(H), gmlp.from_bf16_bits(Wd), workspace=ws) for _ in range(2)]
+    _check(_f64(y[0]), orc.down_rows(H, Wd), "down T=%d K=%d" % (T, K))
+    X, Wg, Wu, Wd = I.generate(T, K, N, seed=T + K)
+    h = [gmlp.gate_up(*(gmlp.from_bf16_bits(a) for a in (X, Wg, Wu)), workspace=ws2) for _ in range(2)]
+    _, ref = orc.gated_mlp_rows(X, Wg, Wu, Wd, return_h=True)
+    _check(_f64(h[0]), ref, "H T=%d K=%d" % (T, K))
+    for w, (a, b) in ((ws, y), (ws2, h)):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+        assert int(torch.count_nonzero(w.buffer[:128 * 1024])) == 0  # counters back at zero
+
+
 @pytest.mark.parametrize("T", [16, 70])
 def test_stream_specials(T):
     # A row with a NaN, a weight column with an infinity: each stays in its
