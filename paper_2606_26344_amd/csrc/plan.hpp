@@ -165,6 +165,7 @@ struct Step {
     int tile_base = 0, tile_count = 0;
     int tail_tiles = 0, tail_splits = 1, tail_k_split = 0;
     int64_t block_macs = 0; // GEMM: multiply-adds of one block of the main launch, at the splits that fill a round
+    double est_us = 0.0;    // GEMM: estimated time of the main launch (split_time)
 };
 
 // The split part of a step with a tail: its last tail_tiles tiles, split
@@ -237,11 +238,21 @@ void choose_splits(Step &s, int tiles, int target, int tile_k, int min_tiles)
     s.splits = (int)cdiv(s.K, s.k_split);
 }
 
-// Splits of K above 128 tokens: the count up to that of choose_splits with the
-// least estimated time.  A k-tile takes its staged bytes at 50 GB/s per CU (what
+// Estimated time (us) of a GEMM step of `tiles` tiles in `splits` splits of
+// `ktiles` k-tiles: a k-tile takes its staged bytes at 50 GB/s per CU (what
 // the ring kernels reach: 0.66 us for the 128 x 128 down tiles, 0.98 for the
 // gate/up ones), an exchange 4 us, the partial tile of each split read by the
 // last block at 54 GB/s, and all blocks' partial tiles written at 8 TB/s.
+double split_time(int64_t ktiles, int64_t splits, int64_t tiles, size_t stage_bytes, size_t tile_bytes)
+{
+    const double t = (double)ktiles * (double)stage_bytes / 50e3;
+    if (splits == 1)
+        return t;
+    return t + 4.0 + (double)splits * (double)tile_bytes / 54e3 + (double)(splits * tiles) * (double)tile_bytes / 8e6;
+}
+
+// Splits of K above 128 tokens: the count up to that of choose_splits with the
+// least estimated time.
 // Splitting to fill the chip whatever K is, as few as two k-tiles per split,
 // spent most of a small step in the exchange.  Measured, before and after, us:
 // down T = 328, D = 880, F = 2296 20.1 -> 15.4 (12 splits to 4); the whole MLP
@@ -256,10 +267,8 @@ void choose_splits_by_time(Step &s, int tiles, int target, int tile_k, size_t st
     double best = 0.0;
     int64_t per = ktiles;
     for (int64_t n = 1; n <= most; ++n) {
-        const int64_t p = cdiv(ktiles, n), used = cdiv(ktiles, p);
-        double t = (double)p * (double)stage_bytes / 50e3; // us
-        if (used > 1)
-            t += 4.0 + (double)used * (double)tile_bytes / 54e3 + (double)(used * tiles) * (double)tile_bytes / 8e6;
+        const int64_t p = cdiv(ktiles, n);
+        const double t = split_time(p, cdiv(ktiles, p), tiles, stage_bytes, tile_bytes);
         if (n == 1 || t < best) {
             best = t;
             per = p;
@@ -285,6 +294,9 @@ void gemm_step(Step &s, Kind kind, int M, int N, int K, int nw, bool allow_split
     s.tail_tiles = 0;
     s.tail_splits = 1;
     s.tail_k_split = 0;
+    const size_t stage_bytes = (size_t)(S::BMW * nw + S::BN) * S::BK * 2;
+    // Partial sums of whole tiles (padded), [split][tile][wave][piece][lane].
+    const size_t tile_bytes = (size_t)S::BMW * S::BN * nw * sizeof(float);
     int reserve = 1; // splits the workspace holds partial sums for
     int macs_rows = K;
     if (allow_split) {
@@ -292,8 +304,7 @@ void gemm_step(Step &s, Kind kind, int M, int N, int K, int nw, bool allow_split
         reserve = s.splits;
         macs_rows = s.k_split;
         if (N > 128 && kind != K_GEMM_DN_L && kind != K_GEMM_DN_X)
-            choose_splits_by_time(s, tiles, kBlockTarget, S::BK, (size_t)(S::BMW * nw + S::BN) * S::BK * 2,
-                                  (size_t)S::BMW * S::BN * nw * sizeof(float));
+            choose_splits_by_time(s, tiles, kBlockTarget, S::BK, stage_bytes, tile_bytes);
     } else {
         s.splits = 1;
         s.k_split = K;
@@ -313,11 +324,10 @@ void gemm_step(Step &s, Kind kind, int M, int N, int K, int nw, bool allow_split
     }
     s.blocks = s.tile_count * s.splits;
     s.block_macs = (int64_t)S::BMW * S::BN * nw * macs_rows;
+    s.est_us = split_time(cdiv(s.k_split, S::BK), s.splits, tiles, stage_bytes, tile_bytes);
     s.threads = S::NTHREADS;
     s.counters = std::max(s.splits > 1 ? tiles : 0, s.tail_tiles);
-    // Partial sums of whole tiles (padded), [split][tile][wave][piece][lane];
-    // the tail tiles use the space of a split step's partial sums.
-    const size_t tile_bytes = (size_t)S::BMW * S::BN * nw * sizeof(float);
+    // The tail tiles use the space of a split step's partial sums.
     // Space for `reserve` splits (which covers fewer), so that the workspace of a
     // shape, and which other shapes it serves, does not depend on the estimate.
     s.partial_bytes = std::max(reserve > 1 ? (size_t)reserve * tiles * tile_bytes : 0,
@@ -651,19 +661,27 @@ Plan make_plan(int64_t T, int64_t D, int64_t F, int path)
             stream_step(p.down, wm, (int)D, (int)T, (int)F, false);
     }
     // 257 to 384 tokens: two 192-token down tiles split over K where there
-    // are 64 to 128 of them (so that at least two splits fill a round) and
-    // a block's work is at most 95% of what the rules above give it.
+    // are 64 to 128 of them (so that at least two splits fill a round), a
+    // block's work at those splits is at most 95% of what the rules above
+    // give it, and, against the 128 x 128 tiles, the estimated time at the
+    // splits that run is less too.
     // Measured: down at D = 4096, F = 14336 T = 257 61.9 -> 58.7 us, 320
     // 62.4 -> 59.9, 384 62.9 -> 60.4 (93% of the work); D = 8192, F = 28672,
     // T = 320 221.9 -> 195.0 (75%); slower at equal work (D = 5120,
     // F = 13824, T = 300: 69.5 -> 74.7) and with 32 tiles (D = 2048,
-    // F = 8192, T = 300: 27.5 -> 34.4).
+    // F = 8192, T = 300: 27.5 -> 34.4).  The work alone does not tell where K
+    // is short: such steps are not split, and then the 128-token tiles have
+    // a third less of it on more CUs.
     const int64_t down192 = cdiv(T, DownMid192::BN) * cdiv(D, DownMid192::BMW);
     if (T > 256 && T <= 2 * DownMid192::BN && down192 >= 64 && down192 <= kBlockTarget / 2) {
         Step mid;
         gemm_step<DownMid192>(mid, K_GEMM_DN_Y, (int)D, (int)T, (int)F, 1, true, kGroupDown);
-        if (p.down.tail_tiles == 0 && p.down.blocks <= kBlockTarget && mid.block_macs * 20 <= p.down.block_macs * 19)
-            p.down = mid;
+        if (p.down.tail_tiles == 0 && p.down.blocks <= kBlockTarget && mid.block_macs * 20 <= p.down.block_macs * 19) {
+            if (p.down.kind != K_GEMM_DN_S || mid.est_us < p.down.est_us)
+                p.down = mid;
+            else // the shape's workspace holds the partial sums of either
+                p.down.partial_bytes = std::max(p.down.partial_bytes, mid.partial_bytes);
+        }
     }
     // From 513 tokens, where the 256-token gate/up tiles leave a last round
     // of split-K tail tiles and the last token tile is at most half full,

@@ -26,6 +26,22 @@ def test_splits_cover_k_and_fit_a_round(T, D, F):
         assert splits == 1 or grid <= 256 or "false>" in name
 
 
+# Down steps of 257 to 384 tokens and 64 to 128 192-token tiles: where K is
+# short the steps are hardly split, and unsplit 192-token tiles are longer blocks
+# on fewer CUs than the 128-token ones.
+SHORT_K = [(300, 4096, 1024), (300, 6144, 1024), (384, 4096, 1032), (300, 4096, 512), (257, 8192, 768)]
+LONG_K = [(257, 4096, 14336), (300, 4096, 4096), (384, 4096, 14336), (320, 8192, 28672)]
+
+
+@pytest.mark.parametrize("T,D,F", SHORT_K + LONG_K)
+def test_down_tile_of_257_to_384_tokens(T, D, F):
+    name, grid, _, splits = gmlp.describe(T, D, F)[-1]
+    tokens = 128 if (T, D, F) in SHORT_K else 192
+    tile = {128: "GemmShape<1, 2, 2, 2, 2, 4, 64>", 192: "GemmShape<1, 4, 1, 1, 6, 3, 64>"}[tokens]
+    assert tile in name and grid == -(-T // tokens) * -(-D // 128) * splits, (name, grid, splits)
+    assert splits > 1 or tokens == 128
+
+
 def _check(got, ref, what):
     assert np.all(np.isfinite(got)), what
     ratio = float(np.max(np.abs(got - ref) / (TOL * (np.abs(ref) + np.sqrt(np.mean(ref ** 2))))))
@@ -35,7 +51,7 @@ def _check(got, ref, what):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("T,D,F", [(390, 256, 512), (211, 1032, 2056), (140, 1032, 4104), (170, 520, 1544),
-                                   (330, 1032, 4848), (768, 2760, 1544)])
+                                   (330, 1032, 4848), (768, 2760, 1544), (300, 4096, 520)])
 def test_split_kernels(orc, T, D, F):
     X, Wg, Wu, Wd = I.generate(T, D, F, seed=T)
     x, wg, wu, wd = (gmlp.from_bf16_bits(a) for a in (X, Wg, Wu, Wd))
