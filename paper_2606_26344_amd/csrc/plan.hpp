@@ -433,14 +433,21 @@ auto with_stream_tile(const Step &s, F f)
 
 // Splits of the 64-column tiles keep at least 512 rows (measured at
 // D = 1024, F = 4096, T = 64, splits of 256 rows against 512: down 14.3 -> 11.5
-// us, gate/up 14.8 -> 13.7), those of the 128-column tiles 256.
+// us, gate/up 14.8 -> 13.7), those of the 128-column tiles 256.  A K of 513
+// to 1408 rows would then stay whole or in splits of up to 768 rows, which the
+// gate/up step, two weights a wave, feels (T = 31, D = 856, F = 264 12.8 us
+// unsplit, 9.1 in three; T = 113, D = 1336, F = 272 23.0 in two splits, 19.1 in
+// three; the ring 10.5 and 19.9): it splits up to 1024 rows into 256 and more, up to
+// 1408 into 384 and more.  Longer K: T = 69, D = 6888, F = 544 11 splits 20.7, 27
+// splits 25.0.
 void stream_step(Step &s, int wm, int M, int N, int K, bool gate_up)
 {
     s.stream_wm = wm;
     s.N = N;
     with_stream_tile(s, [&](auto tn, auto w) {
         constexpr int TN = decltype(tn)::value, WM = decltype(w)::value;
-        constexpr int min_k_tiles = WM == 4 ? 2 : 4;
+        const int ktiles = (int)cdiv(K, 128);
+        const int min_k_tiles = WM == 4 ? 2 : !gate_up || ktiles <= 4 || ktiles > 11 ? 4 : ktiles <= 8 ? 2 : 3;
         if (gate_up)
             gemm_step<StreamGateUp<TN, WM>>(s, K_STREAM_GU, M, N, K, 2, true, 1, min_k_tiles);
         else
