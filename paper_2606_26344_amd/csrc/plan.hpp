@@ -385,6 +385,41 @@ using StreamDown = GemmShape<1, WM, 1, 1, TN, WM == 4 ? 1 : 2, 128>;
 constexpr int kStreamMaxTokens = 128;
 constexpr int kStreamWideTokens = 16; // the 128-column tiles: one 16-token tile
 
+// Steps of small weights on which the 64-column streaming tiles are slower
+// than the ring's.  Measured, ring against streaming, us:
+//   * gate/up above 80 tokens where K is a few k-tiles, too few for the ring to
+//     split: the sum over the waves costs more than it saves.  T = 122, K = 8,
+//     F = 4032 6.6 -> 8.5; T = 120, K = 192, F = 80 7.6 -> 9.9; T = 88, K = 48,
+//     F = 4000 6.8 -> 7.1; from T = 97, K = 200 on 12.1 -> 10.1, from T = 81, K = 72
+//     (F = 1000) 7.6 -> 7.2.
+//   * outputs of 8193 to 16384 columns: 129 to 256 64-column tiles, one unsplit
+//     block each, where the ring's 128-column tiles split K two or three ways,
+//     which tells where K is long.  Gate/up T = 120, F = 8704: K = 904 24.5 -> 24.0,
+//     1200 26.4 -> 27.9, 1920 29.2 -> 39.5; T = 80: K = 1360 26.1 -> 25.1, 1600 26.8 ->
+//     28.1.  Down T = 48, D = 9216: K = 1200 13.9 -> 13.1, 1400 14.4 -> 14.8,
+//     1600 14.6 -> 16.1.  From 76 ring tiles on (9600 columns) its three splits
+//     fill the chip and gain less: down T = 48, D = 10240, K = 1504 15.6 -> 14.5.
+//   * down steps of 16385 to 32768 columns, more than one round of 64-column
+//     tiles and one of 128-column tiles: T = 20, D = 20480 K = 136 5.9 -> 5.0,
+//     256 6.7 -> 7.2, 504 9.0 -> 10.0; T = 72, K = 136 8.3 -> 9.4.  Above, both take
+//     several rounds, and up to 80 tokens the streaming tiles win again (D = 49152,
+//     K = 320: T = 64 19.3 -> 14.3, 90 20.1 -> 20.9; T = 120, D = 33000, K = 504 24.6 ->
+//     29.9).
+bool stream_slower(int64_t n, int64_t M, int64_t K, bool gate_up)
+{
+    if (gate_up && n > 80 && K <= (n > 96 ? 192 : 64))
+        return true;
+    const int64_t round = (int64_t)64 * kBlockTarget; // columns of one round of 64-column tiles
+    if (M <= round / 2)
+        return false;
+    if (M > round)
+        return M <= 2 * round ? n > 64 || K > 192 : n > 80;
+    const bool full = M > 9600; // three splits of the ring's tiles fill the chip
+    if (gate_up)
+        return K > (n > 32 && n <= 96 ? 1400 : full ? 1200 : 1100);
+    return K > (full && n <= 96 ? 1504 : 1280);
+}
+
 // Which streaming tile (WM) a step of n tokens and an M x K weight takes on
 // the automatic path, 0: the LDS-ring tiles.  With small weights a step is
 // bound by its latency: the ring's barriers and above all the split-K
@@ -413,7 +448,7 @@ int stream_width(int64_t n, int64_t M, int64_t K, bool gate_up)
     const int64_t weight = M * K;
     if (n <= kStreamWideTokens && weight > (int64_t(1) << 22))
         return weight <= (gate_up ? int64_t(3) << 23 : int64_t(1) << 26) ? 4 : 0;
-    return weight <= (int64_t(1) << 24) ? 2 : 0;
+    return weight <= (int64_t(1) << 24) && !stream_slower(n, M, K, gate_up) ? 2 : 0;
 }
 
 // f(TN, WM) as integral constants, for the streaming tile of a step.

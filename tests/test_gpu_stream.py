@@ -48,7 +48,7 @@ def _is_stream(line):
 
 # T, D, F: 64-column tiles in both steps unless noted.
 SHAPES = [(T, 264, 520) for T in (6, 15, 16, 17, 31, 32, 33, 48, 49, 64, 65, 80, 81, 96, 97, 112, 113, 128)]
-SHAPES += [(24, 8, 8), (7, 8, 1032), (40, 1032, 8), (128, 40, 72),   # waves without a batch, one short tile
+SHAPES += [(24, 8, 8), (7, 8, 1032), (40, 1032, 8), (80, 40, 72), (128, 40, 72),   # waves without a batch, one short tile
            (16, 2056, 3080), (9, 1032, 4104), (16, 3080, 2056),      # 128-column tiles (weights above 2^22), short last tile
            (51, 1032, 4104), (100, 2056, 1544), (128, 1544, 4168),    # several splits, ragged K
            (64, 4104, 264), (90, 136, 11000)]
@@ -57,7 +57,8 @@ SHAPES += [(24, 8, 8), (7, 8, 1032), (40, 1032, 8), (128, 40, 72),   # waves wit
 @pytest.mark.parametrize("T,D,F", SHAPES, ids=["T%dD%dF%d" % s for s in SHAPES])
 def test_stream_tiles(orc, T, D, F):
     plan = gmlp.describe(T, D, F)
-    assert all(_is_stream(line) for line in plan), plan
+    # (128 tokens over 40 rows: the gate/up step runs on the ring, which is faster there.)
+    assert [_is_stream(line) for line in plan] == [(T, D) != (128, 40), True], plan
     X, Wg, Wu, Wd = I.generate(T, D, F, seed=T + D + F)
     x, wg, wu, wd = (gmlp.from_bf16_bits(a) for a in (X, Wg, Wu, Wd))
     ws = gmlp.Workspace(T, D, F)

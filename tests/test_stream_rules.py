@@ -5,8 +5,10 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 from paper_2606_26344_amd import gmlp
 from paper_2606_26344_amd import inputs as I
+from paper_2606_26344_amd import softmax_matmul as smm
 
 TOL = 1e-2
 
@@ -28,6 +30,27 @@ def test_gate_up_splits(T, D, F, splits):
     assert line[1] == -(-F // 64) * splits
 
 
+# (T, columns, K, streaming): both sides of each line of the rule.
+GATE_UP = [(81, 1000, 64, False), (81, 1000, 72, True), (80, 1000, 64, True), (96, 80, 64, False),
+           (97, 80, 192, False), (97, 1000, 200, True), (128, 3144, 8, False), (128, 3144, 192, False),
+           (20, 8200, 1104, False), (20, 8200, 1096, True), (120, 8704, 1920, False), (48, 8704, 1400, True),
+           (48, 8704, 1408, False), (97, 9608, 1200, True), (97, 9608, 1208, False), (120, 8192, 2048, True)]
+DOWN = [(48, 9216, 1280, True), (48, 9216, 1288, False), (96, 9608, 1504, True), (96, 9608, 1512, False),
+        (97, 9608, 1280, True), (97, 9608, 1288, False), (64, 16384, 1016, True), (64, 16392, 192, True),
+        (64, 16392, 200, False), (65, 16392, 16, False), (80, 32776, 16, True), (81, 32776, 16, False),
+        (120, 8, 192, True), (128, 8192, 2048, True)]
+
+
+@pytest.mark.parametrize("T,F,D,stream", GATE_UP)
+def test_gate_up_tile(T, F, D, stream):
+    assert _stream(gmlp.describe(T, D, F)[0]) == stream
+
+
+@pytest.mark.parametrize("T,D,F,stream", DOWN)
+def test_down_tile(T, D, F, stream):
+    assert _stream(gmlp.describe(T, D, F)[1]) == stream
+
+
 def _check(got, ref, what):
     assert np.all(np.isfinite(got)), what
     ratio = float(np.max(np.abs(got - ref) / (TOL * (np.abs(ref) + np.sqrt(np.mean(ref ** 2))))))
@@ -45,3 +68,28 @@ def test_gate_up_split_kernels(orc, T, D, F, splits):
     assert torch.equal(h[0].view(torch.int16), h[1].view(torch.int16))
     _, ref = orc.gated_mlp_rows(X, Wg, Wu, Wd, return_h=True)
     _check(I.bf16_bits_to_f32(gmlp.to_bf16_bits(h[0])).astype(np.float64), ref, "T=%d D=%d F=%d" % (T, D, F))
+
+
+# The steps that went back to the ring, one of each kind, with the options.
+@pytest.mark.gpu
+@pytest.mark.parametrize("T,D,F", [(96, 64, 1000), (128, 8, 3144), (97, 192, 80), (120, 1912, 8712), (20, 1104, 8200)])
+def test_gate_up_on_the_ring(orc, T, D, F):
+    assert not _stream(gmlp.describe(T, D, F)[0])
+    variant = dict(activation="swish", beta=1.702, rmsnorm=True, eps=1e-5)
+    X, Wg, Wu, Wd = I.generate(T, D, F, seed=T + D)
+    h = gmlp.gate_up(*(gmlp.from_bf16_bits(a) for a in (X, Wg, Wu)), workspace=gmlp.Workspace(T, D, F), **variant)
+    torch.cuda.synchronize()
+    rows = np.unique(np.concatenate([I.sample_rows(T, 12), np.arange(T - 2, T)]))
+    _, ref = orc.gated_mlp_rows(X, Wg, Wu, Wd, rows=rows, return_h=True, **variant)
+    _check(I.bf16_bits_to_f32(gmlp.to_bf16_bits(h)[rows]).astype(np.float64), ref, "T=%d D=%d F=%d" % (T, D, F))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,K,N", [(48, 1288, 9216), (65, 16, 16392), (64, 200, 16392), (81, 72, 32776)])
+def test_softmax_matmul_on_the_ring(M, K, N):
+    assert not _stream(smm.describe(M, K, N)[1])
+    X, Y = I.generate_softmax_matmul(M, K, N, seed=M)
+    z = smm.softmax_matmul(gmlp.from_bf16_bits(X), gmlp.from_bf16_bits(Y), workspace=smm.make_workspace(M, K, N))
+    torch.cuda.synchronize()
+    _check(I.bf16_bits_to_f32(gmlp.to_bf16_bits(z)).astype(np.float64), oracle.softmax_matmul_rows(X, Y),
+           "M=%d K=%d N=%d" % (M, K, N))
