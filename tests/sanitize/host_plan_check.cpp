@@ -120,6 +120,28 @@ int main()
             }
     EXPECT(plans > 1000, "only %d plans", plans);
 
+    // Token splits of the gate/up step on the automatic path: the rest rows
+    // run the kernels of that path (GEMV up to 5 rows, streaming tiles of small
+    // weights), which the explicit MFMA path does not, and whose partial sums
+    // can be larger than any other step's (by 1.9 MB at T = 1794, D = 14808,
+    // F = 17344).  The layout holds them.
+    int gemv_rests = 0, stream_rests = 0;
+    for (int64_t T : {513, 515, 517, 560, 640, 770, 1026, 1100, 1600, 1794, 2306, 2564, 3075})
+        for (int64_t D : {264, 1032, 2048, 4104, 8192, 14808, 28672})
+            for (int64_t F : {4104, 8192, 10248, 12288, 14344, 17344, 28672}) {
+                const Layout l = make_layout(T, D, F);
+                const Plan p = make_plan(T, D, F, GMLP_PATH_AUTO);
+                if (!p.rest_row)
+                    continue;
+                for (const Step *s : {&p.gate_up, &p.gate_up_rest, &p.down}) {
+                    check_step(*s, l, T, D, F);
+                    EXPECT(s->counters <= l.counters, "counters %d of %d", s->counters, l.counters);
+                }
+                gemv_rests += p.gate_up_rest.kind == K_GEMV;
+                stream_rests += p.gate_up_rest.kind == K_STREAM_GU;
+            }
+    EXPECT(gemv_rests > 10 && stream_rests > 10, "%d GEMV and %d streaming rests", gemv_rests, stream_rests);
+
     // Validation: rejected shapes and arguments never reach planning.
     const char *A = reinterpret_cast<const char *>(uintptr_t(1) << 40);
     const int64_t G = int64_t(1) << 34;
