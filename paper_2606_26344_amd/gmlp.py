@@ -153,12 +153,19 @@ def _empty(shape, dtype, device, stream=None) -> torch.Tensor:
         return torch.empty(shape, dtype=dtype, device=device)
 
 
+# The device of the stream a call runs on, for torch: the current one, and under
+# torch.cuda.stream(stream) that stream's.  A call's scratch is memory of this
+# device whichever one the arguments are on, since only the call's own stream
+# orders the reuse of the memory after the call.
+_CALL_DEVICE = "cuda"
+
+
 def _scratch(nbytes: int, rows: int, device, stream, plain: bool, invalid: str):
     """Memory for one call's workspace from torch's caching allocator, as
     (tensor to keep until the call is enqueued, 256-byte aligned address);
     (None, None) where the call takes none (no rows, or a shape that the
     library refuses).  Its contents are undefined: the call is made with
-    FRESH_WORKSPACE.  hipMallocAsync in the library costs 9 us of host time a
+    FRESH_WORKSPACE.  ``device`` is _CALL_DEVICE.  hipMallocAsync in the library costs 9 us of host time a
     call and, since its pool gives its memory back whenever the device is
     synchronised, 30 to 40 us more on the first call after that.  ``plain``
     calls (those of the C entry points that allocate) report a refused shape
@@ -283,7 +290,7 @@ def forward(x: torch.Tensor, wg: torch.Tensor, wu: torch.Tensor, wd: torch.Tenso
     st = _stream(stream)
     if workspace is None:
         nbytes = workspace_size(T, D, F)
-        keep, ws = _scratch(nbytes, T, dev, stream, variant is None and code == PATH_AUTO,
+        keep, ws = _scratch(nbytes, T, _CALL_DEVICE, stream, variant is None and code == PATH_AUTO,
                             "invalid shape T=%d D=%d F=%d" % (T, D, F))
         code |= FRESH_WORKSPACE
     else:
@@ -333,7 +340,7 @@ def gate_up(x: torch.Tensor, wg: torch.Tensor, wu: torch.Tensor,
     st = _stream(stream)
     if workspace is None:
         nbytes = workspace_size(T, D, F)
-        keep, ws = _scratch(nbytes, T, dev, stream, plain and code == PATH_AUTO,
+        keep, ws = _scratch(nbytes, T, _CALL_DEVICE, stream, plain and code == PATH_AUTO,
                             "invalid shape T=%d D=%d F=%d" % (T, D, F))
         if code not in (PATH_FUSED, PATH_FUSED_MFMA):  # refused by the library
             code |= FRESH_WORKSPACE
@@ -364,7 +371,8 @@ def down(h: torch.Tensor, wd: torch.Tensor, out: Optional[torch.Tensor] = None,
     st = _stream(stream)
     if workspace is None:
         nbytes = workspace_size(T, D, F)
-        keep, ws = _scratch(nbytes, T, dev, stream, code == PATH_AUTO, "invalid shape T=%d D=%d F=%d" % (T, D, F))
+        keep, ws = _scratch(nbytes, T, _CALL_DEVICE, stream, code == PATH_AUTO,
+                            "invalid shape T=%d D=%d F=%d" % (T, D, F))
         if code not in (PATH_FUSED, PATH_FUSED_MFMA):  # refused by the library
             code |= FRESH_WORKSPACE
     else:

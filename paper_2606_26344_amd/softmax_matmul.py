@@ -20,7 +20,7 @@ from typing import Optional
 
 import torch
 
-from .gmlp import (FRESH_WORKSPACE, PATH_AUTO, PATH_FUSED, PATH_FUSED_MFMA, _PATHS, Workspace, _check, _empty,
+from .gmlp import (_CALL_DEVICE, FRESH_WORKSPACE, PATH_AUTO, PATH_FUSED, PATH_FUSED_MFMA, _PATHS, Workspace, _check, _empty,
                    _expect, _parse_plan, _ptr, _scratch, _stream, library)
 
 
@@ -62,7 +62,8 @@ def softmax_matmul(x: torch.Tensor, y: torch.Tensor, out: Optional[torch.Tensor]
     st = _stream(stream)
     if workspace is None:
         nbytes = workspace_size(M, K, N)
-        keep, ws = _scratch(nbytes, M, dev, stream, code == PATH_AUTO, "invalid shape M=%d K=%d N=%d" % (M, K, N))
+        keep, ws = _scratch(nbytes, M, _CALL_DEVICE, stream, code == PATH_AUTO,
+                            "invalid shape M=%d K=%d N=%d" % (M, K, N))
         if code not in (PATH_FUSED, PATH_FUSED_MFMA):  # refused by the library
             code |= FRESH_WORKSPACE
     else:

@@ -123,3 +123,32 @@ def test_a_refused_shape_is_reported_as_before():
     assert gmlp._scratch(1024, 0, "cuda", None, True, "unused") == (None, None)
     with pytest.raises(ValueError, match="invalid shape"):
         gmlp._scratch(0, 4, "cuda", None, False, "invalid shape T=4 D=12 F=16")
+
+
+def test_scratch_is_memory_of_the_device_of_the_stream(monkeypatch):
+    # The arguments on another device than the current one, whose stream the
+    # calls run on: the outputs are allocated on the arguments' device, the
+    # scratch on "cuda", the device of the stream.
+    class Library:
+        def __getattr__(self, name):
+            return lambda *args: 4096 if name.endswith("workspace_size") else 0
+
+    asked = []
+
+    def empty(shape, dtype, device, stream=None):
+        asked.append((dtype, str(device), stream))
+        return torch.empty(shape, dtype=dtype)
+
+    for module in (gmlp, smm):
+        monkeypatch.setattr(module, "library", Library)
+        monkeypatch.setattr(module, "_empty", empty)
+        monkeypatch.setattr(module, "_expect", lambda *args: None)
+        monkeypatch.setattr(module, "_stream", lambda stream: 0)
+    a = torch.empty(16, 16, dtype=torch.bfloat16)
+    for call in (lambda s: gmlp.forward(a, a, a, a, stream=s), lambda s: gmlp.gate_up(a, a, a, stream=s),
+                 lambda s: gmlp.down(a, a, stream=s), lambda s: smm.softmax_matmul(a, a, stream=s),
+                 lambda s: gmlp.forward(a, a, a, a, stream=s, path="mfma", rmsnorm=True)):
+        for stream in (None, "a stream"):
+            asked.clear()
+            call(stream)
+            assert asked == [(torch.bfloat16, "cpu", stream), (torch.uint8, "cuda", stream)]
