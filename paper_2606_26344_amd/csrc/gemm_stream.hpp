@@ -48,11 +48,10 @@ template <class S, int EPI, int NT>
 __device__ __forceinline__ void stream_tile(const GemmParams &p, int block, f32x4 *red)
 {
     __shared__ int s_last;
-    constexpr int NW = S::NW, WPW = S::WPW, NWAVES = S::NWAVES, DEPTH = S::STAGES;
+    constexpr int NW = S::NW, NWAVES = S::NWAVES, DEPTH = S::STAGES;
     constexpr int CPL = S::BMW / 16; // columns per lane
     constexpr int HP = CPL / 4;      // pieces of 4 columns per lane and 16-token tile of a wave's share
     typedef __attribute__((__vector_size__(CPL * 2))) uint32_t Row; // a lane's columns of one row
-    constexpr int KW = NWAVES * WPW / NW; // waves that share the rows of a weight
     static_assert(EPI == EPI_GATE_MUL ? NW == 2 : EPI == EPI_STORE && NW == 1, "gate/up of both weights, or the down step");
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -65,26 +64,24 @@ __device__ __forceinline__ void stream_tile(const GemmParams &p, int block, f32x
     const int m0 = tile * S::BMW;
     const int kb = split * p.k_split;
     const int ke = min(K, kb + p.k_split);
-    const int kw = wave % KW;
-    const uint16_t *w_first = WPW < NW && wave / KW ? p.w1 : p.w0;
     const int nb_all = (ke - kb + 31) >> 5;
-    const int nb = (nb_all - kw + KW - 1) / KW; // batches of this wave: kw, kw + KW, ...
+    const int nb = (nb_all - wave + NWAVES - 1) / NWAVES; // batches of this wave: wave, wave + NWAVES, ...
 
     // Lane offsets within a batch, in bytes; out of range (zeros, no fetch)
     // past the last column and the last token.
     const uint32_t w_voff = m0 + CPL * l16 < M ? (uint32_t)(8 * g * M + CPL * l16) * 2u : kOutOfRange;
     const uint32_t x_voff = (uint32_t)(l16 * K + 8 * g) * 2u;
 
-    // Unit u of a wave is weight u % WPW of its batch u / WPW; DEPTH units are
+    // Unit u of a wave is weight u % NW of its batch u / NW; DEPTH units are
     // in flight.  A unit's registers are loaded again as soon as it has been
     // transposed, ahead of its MFMAs.  The token fragments of the next batch
     // are issued before those loads: loads complete in order, so they never
     // wait for the weights issued behind them.
     constexpr bool WIDE = CPL == 8;
     auto load_w = [&](Row (&v)[8], int b, int w) __attribute__((always_inline)) {
-        const int k0 = kb + 32 * (kw + b * KW);
+        const int k0 = kb + 32 * (wave + b * NWAVES);
         const uint32_t voff = k0 + 8 * g < ke ? w_voff : kOutOfRange; // K and the splits are multiples of 8
-        const __amdgpu_buffer_rsrc_t r = make_rsrc((w == 0 ? w_first : p.w1) + (size_t)min(k0, K - 8) * M + m0);
+        const __amdgpu_buffer_rsrc_t r = make_rsrc((w == 0 ? p.w0 : p.w1) + (size_t)min(k0, K - 8) * M + m0);
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const uint32_t soff = (uint32_t)i * (uint32_t)M * 2u;
@@ -95,7 +92,7 @@ __device__ __forceinline__ void stream_tile(const GemmParams &p, int block, f32x
         }
     };
     auto load_x = [&](u32x4 (&v)[NT], int b) __attribute__((always_inline)) {
-        const int k0 = kb + 32 * (kw + b * KW);
+        const int k0 = kb + 32 * (wave + b * NWAVES);
         const bool in = k0 + 8 * g < ke;
         const __amdgpu_buffer_rsrc_t r = make_rsrc(p.act + min(k0, K - 8));
 #pragma unroll
@@ -105,9 +102,9 @@ __device__ __forceinline__ void stream_tile(const GemmParams &p, int block, f32x
                                                  (uint32_t)(16 * t) * (uint32_t)K * 2u, 0));
     };
 
-    f32x4 acc[WPW][CPL][NT];
+    f32x4 acc[NW][CPL][NT];
 #pragma unroll
-    for (int w = 0; w < WPW; ++w)
+    for (int w = 0; w < NW; ++w)
 #pragma unroll
         for (int i = 0; i < CPL; ++i)
 #pragma unroll
@@ -118,13 +115,13 @@ __device__ __forceinline__ void stream_tile(const GemmParams &p, int block, f32x
     load_x(x[0], 0);
 #pragma unroll
     for (int u = 0; u < DEPTH; ++u)
-        load_w(raw[u], u / WPW, u % WPW);
-    static_assert(2 * WPW % DEPTH == 0, "two batches are whole turns of the ring");
+        load_w(raw[u], u / NW, u % NW);
+    static_assert(2 * NW % DEPTH == 0, "two batches are whole turns of the ring");
     auto batch = [&](auto odd, int b) __attribute__((always_inline)) {
         constexpr int P = decltype(odd)::value;
 #pragma unroll
-        for (int w = 0; w < WPW; ++w) {
-            Row(&rw)[8] = raw[(P * WPW + w) % DEPTH];
+        for (int w = 0; w < NW; ++w) {
+            Row(&rw)[8] = raw[(P * NW + w) % DEPTH];
             bf16x8 a[CPL]; // column i of the lane's 8 rows
 #pragma unroll
             for (int e = 0; e < CPL / 2; ++e) {
@@ -138,9 +135,9 @@ __device__ __forceinline__ void stream_tile(const GemmParams &p, int block, f32x
                 a[2 * e + 1] = __builtin_bit_cast(bf16x8, hi);
             }
             __builtin_amdgcn_sched_barrier(0);
-            if (w + 1 == WPW)
+            if (w + 1 == NW)
                 load_x(x[1 - P], b + 1);
-            load_w(rw, b + (w + DEPTH) / WPW, (w + DEPTH) % WPW);
+            load_w(rw, b + (w + DEPTH) / NW, (w + DEPTH) % NW);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int i = 0; i < CPL; ++i)
@@ -162,56 +159,49 @@ __device__ __forceinline__ void stream_tile(const GemmParams &p, int block, f32x
     // ---- sum over the waves, through LDS ---------------------------------------
     // Lane l's accumulators [i][t] element r are column 4 CPL g + CPL r + i of
     // token 16 t + l16.  Wave r adds up the CPL columns of group r (HP pieces
-    // of 4 columns per token tile) over the waves that hold the weight, in
-    // wave order.  A round moves G token
-    // tiles of RW weights per wave.
-    constexpr int G = S::RED_TILES < NT ? S::RED_TILES : NT;
-    constexpr int RW = WPW == 2 && S::RED_WEIGHTS == 2 ? 2 : 1;
+    // of 4 columns per token tile) over the waves, in wave order.  A round
+    // moves all token tiles of RW weights.
+    constexpr int RW = S::RED_WEIGHTS;
     float sum[NW][NT][CPL];
     auto slot = [&](int src, int w, int t, int r, int h) __attribute__((always_inline)) {
-        return red + ((((src * RW + w) * G + t) * 4 + r) * HP + h) * 64 + lane;
+        return red + ((((src * RW + w) * NT + t) * 4 + r) * HP + h) * 64 + lane;
     };
     auto own = [&](int w, int t, int r, int h) __attribute__((always_inline)) {
         return f32x4{acc[w][4 * h][t][r], acc[w][4 * h + 1][t][r], acc[w][4 * h + 2][t][r], acc[w][4 * h + 3][t][r]};
     };
 #pragma unroll
-    for (int w0 = 0; w0 < WPW; w0 += RW)
-#pragma unroll
-        for (int t0 = 0; t0 < NT; t0 += G) {
-            if (w0 + t0 > 0)
-                __syncthreads();
-#pragma unroll
-            for (int w = 0; w < RW; ++w)
-#pragma unroll
-                for (int t = 0; t < G; ++t)
-                    if (t0 + t < NT)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r)
-#pragma unroll
-                            for (int h = 0; h < HP; ++h)
-                                *slot(wave, w, t, r, h) = own(w0 + w, t0 + t, r, h);
+    for (int w0 = 0; w0 < NW; w0 += RW) {
+        if (w0 > 0)
             __syncthreads();
 #pragma unroll
-            for (int w = 0; w < RW; ++w)
+        for (int w = 0; w < RW; ++w)
 #pragma unroll
-                for (int t = 0; t < G; ++t)
-                    if (t0 + t < NT)
+            for (int t = 0; t < NT; ++t)
 #pragma unroll
-                        for (int ww = 0; ww < NW / WPW; ++ww)
+                for (int r = 0; r < 4; ++r)
 #pragma unroll
-                            for (int h = 0; h < HP; ++h) {
-                                f32x4 s = *slot(ww * KW, w, t, wave, h);
+                    for (int h = 0; h < HP; ++h)
+                        *slot(wave, w, t, r, h) = own(w0 + w, t, r, h);
+        __syncthreads();
 #pragma unroll
-                                for (int q = 1; q < KW; ++q)
-                                    s += *slot(ww * KW + q, w, t, wave, h);
+        for (int w = 0; w < RW; ++w)
 #pragma unroll
-                                for (int e = 0; e < 4; ++e)
-                                    sum[w0 + w + ww][t0 + t][4 * h + e] = s[e];
-                            }
-        }
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int h = 0; h < HP; ++h) {
+                    f32x4 s = *slot(0, w, t, wave, h);
+#pragma unroll
+                    for (int q = 1; q < NWAVES; ++q)
+                        s += *slot(q, w, t, wave, h);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        sum[w0 + w][t][4 * h + e] = s[e];
+                }
+    }
 
     // ---- sum over the splits, by the last block of the tile ---------------------
     constexpr int PIECES = NW * NT * HP; // of this wave
+    static_assert(PIECES <= 16, "two splits in flight at least");
     if (p.splits > 1) {
         const __amdgpu_buffer_rsrc_t prs = make_rsrc(p.partial);
         const uint32_t lane_off = lane * 16;
@@ -246,7 +236,7 @@ __device__ __forceinline__ void stream_tile(const GemmParams &p, int block, f32x
         // real ones (down step with whole groups only: D = 1032, F = 1032, T = 8,
         // two splits and 31 spare loads a piece, 10.1 us against 7.0; D = 1024,
         // F = 4096, T = 16, eight splits, 11.0 against 7.6).
-        constexpr int C = PIECES >= 32 ? 1 : 32 / PIECES;
+        constexpr int C = 32 / PIECES;
         const int others = p.splits - 1;
         f32x4 tot[PIECES];
 #pragma unroll
@@ -283,7 +273,7 @@ __device__ __forceinline__ void stream_tile(const GemmParams &p, int block, f32x
         while (s0 + 2 < others)
             add_group(std::integral_constant<int, (C < 8 ? C : 8)>{});
         if (s0 < others)
-            add_group(std::integral_constant<int, (C < 2 ? C : 2)>{});
+            add_group(std::integral_constant<int, 2>{});
         if (split == others)
 #pragma unroll
             for (int q = 0; q < PIECES; ++q)

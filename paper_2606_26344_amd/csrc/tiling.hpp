@@ -60,23 +60,20 @@ struct GemmShape {
 
 // A streaming configuration (BK = 128: the rows of one batch of each of the
 // block's 4 waves; gemm_stream.hpp): no LDS ring, STAGES batches of 32 rows in
-// flight per wave in registers, one token tile of TN x 32 tokens, 128 columns
-// per weight.  Each wave streams both weights of a gate/up tile up to 64
-// tokens (each X fragment then serves both); above, the accumulators of one
-// weight take the registers, and two waves take each weight.
+// flight per wave in registers, one token tile of TN x 32 tokens, 64 columns
+// (or 128, of one 32-token tile) per weight.  Each wave streams both weights of a
+// gate/up tile, so that each X fragment serves both.
 template <int NW_, int WM_, int WN_, int TM_, int TN_, int STAGES_>
 struct GemmShape<NW_, WM_, WN_, TM_, TN_, STAGES_, 128> {
     static constexpr int NW = NW_, WM = WM_, WN = WN_, TM = TM_, TN = TN_, STAGES = STAGES_;
     static constexpr int BK = 128;
     static constexpr int NWAVES = 4, NTHREADS = 256;
     static constexpr int BMW = WM * TM * 32, BN = WN * TN * 32;
-    static constexpr int WPW = NW == 2 && TN * BMW <= 256 ? 2 : 1; // weights per wave
-    // 16-token tiles per round of the sum over the waves (4 pieces of 1 KB per
-    // 64 columns each), and its LDS bytes.
-    static constexpr int RED_TILES = 2 * TN * BMW <= 512 ? 2 * TN : 512 / BMW;
-    static constexpr int RED_WEIGHTS = WPW == 2 && 2 * RED_TILES * BMW <= 512 ? 2 : 1; // of a wave, per round
-    static constexpr int RED_BYTES = NWAVES * RED_WEIGHTS * RED_TILES * (BMW / 16) * 1024;
-    static_assert(WN == 1 && TM == 1 && (BMW == 64 || BMW == 128) && TN >= 1 && TN <= 4, "64 or 128 columns, up to 128 tokens");
+    // Weights per round of the sum over the waves (4 pieces of 1 KB per 64
+    // columns and 16 tokens each, of every wave), and its LDS bytes: at most 128 KB.
+    static constexpr int RED_WEIGHTS = NW == 2 && 2 * TN * BMW <= 256 ? 2 : 1;
+    static constexpr int RED_BYTES = NWAVES * RED_WEIGHTS * 2 * TN * (BMW / 16) * 1024;
+    static_assert(WN == 1 && TM == 1 && (BMW == 64 || (BMW == 128 && TN == 1)) && TN >= 1 && TN <= 4, "64 columns and up to 128 tokens, or 128 and 32");
     static_assert(STAGES == 1 || STAGES == 2, "units in flight per wave");
 };
 
