@@ -392,11 +392,15 @@ constexpr int kStreamWideTokens = 16; // the 128-column tiles: one 16-token tile
 //     F = 4032 6.6 -> 8.5; T = 120, K = 192, F = 80 7.6 -> 9.9; T = 88, K = 48,
 //     F = 4000 6.8 -> 7.1; from T = 97, K = 200 on 12.1 -> 10.1, from T = 81, K = 72
 //     (F = 1000) 7.6 -> 7.2.
+//   * gate/up above 96 tokens, narrow outputs over 513 to 576 rows, one batch past
+//     what four rounds of the waves take and three splits of the ring: T = 128,
+//     K = 568 F = 264 13.9 -> 17.0, F = 2728 16.9 -> 17.9; K = 600, F = 264 16.9 -> 16.4;
+//     T = 97, F = 1544 15.6 -> 16.4, F = 2728 16.7 -> 16.4.
 //   * outputs of 8193 to 16384 columns: 129 to 256 64-column tiles, one unsplit
 //     block each, where the ring's 128-column tiles split K two or three ways,
 //     which tells where K is long.  Gate/up T = 120, F = 8704: K = 904 24.5 -> 24.0,
 //     1200 26.4 -> 27.9, 1920 29.2 -> 39.5; T = 80: K = 1360 26.1 -> 25.1, 1600 26.8 ->
-//     28.1.  Down T = 48, D = 9216: K = 1200 13.9 -> 13.1, 1400 14.4 -> 14.8,
+//     28.1; T = 50, F = 9216: K = 1400 22.4 -> 24.0.  Down T = 48, D = 9216: K = 1200 13.9 -> 13.1, 1400 14.4 -> 14.8,
 //     1600 14.6 -> 16.1.  From 76 ring tiles on (9600 columns) its three splits
 //     fill the chip and gain less: down T = 48, D = 10240, K = 1504 15.6 -> 14.5.
 //   * down steps of 16385 to 32768 columns, more than one round of 64-column
@@ -409,6 +413,8 @@ bool stream_slower(int64_t n, int64_t M, int64_t K, bool gate_up)
 {
     if (gate_up && n > 80 && K <= (n > 96 ? 192 : 64))
         return true;
+    if (gate_up && n > 96 && K > 512 && K <= 576 && M > 128 && M <= (n > 112 ? 2752 : 1600))
+        return true;
     const int64_t round = (int64_t)64 * kBlockTarget; // columns of one round of 64-column tiles
     if (M <= round / 2)
         return false;
@@ -416,7 +422,7 @@ bool stream_slower(int64_t n, int64_t M, int64_t K, bool gate_up)
         return M <= 2 * round ? n > 64 || K > 192 : n > 80;
     const bool full = M > 9600; // three splits of the ring's tiles fill the chip
     if (gate_up)
-        return K > (n > 32 && n <= 96 ? 1400 : full ? 1200 : 1100);
+        return K > (n > 32 && n <= 96 ? (full ? 1400 : 1300) : (full ? 1200 : 1100));
     return K > (full && n <= 96 ? 1504 : 1280);
 }
 
@@ -466,23 +472,50 @@ auto with_stream_tile(const Step &s, F f)
     }
 }
 
-// Splits of the 64-column tiles keep at least 512 rows (measured at
-// D = 1024, F = 4096, T = 64, splits of 256 rows against 512: down 14.3 -> 11.5
-// us, gate/up 14.8 -> 13.7), those of the 128-column tiles 256.  A K of 513
-// to 1408 rows would then stay whole or in splits of up to 768 rows, which the
-// gate/up step, two weights a wave, feels (T = 31, D = 856, F = 264 12.8 us
-// unsplit, 9.1 in three; T = 113, D = 1336, F = 272 23.0 in two splits, 19.1 in
-// three; the ring 10.5 and 19.9): it splits up to 1024 rows into 256 and more, up to
-// 1408 into 384 and more.  Longer K: T = 69, D = 6888, F = 544 11 splits 20.7, 27
-// splits 25.0.
+// Fewest 128-row k-tiles in a split of the streaming tiles.  Those of 64 columns
+// keep at least 512 rows (measured at D = 1024, F = 4096, T = 64, splits of 256
+// rows against 512: down 14.6 and 11.5 us, gate/up 14.7 and 14.4; gate/up at
+// T = 96 18.7 and 16.5), those of 128 columns 256.  A K of 513 to 1408 rows would
+// then stay whole or in splits of up to 768 rows, which the gate/up step, two
+// weights a wave, feels while its blocks are few; above 96 tokens, where a split
+// adds 64 KB a tile to the exchange, these have to be fewer.  Unsplit or in splits
+// of 512 rows and so, us, with the ring's time:
+//   K = 577 to 640, two splits: T = 128, K = 600, F = 264 17.6, 16.4 (16.9); F = 2048
+//     16.9, 17.4; up to 64 tokens no gain.
+//   K = 641 to 896, three: T = 31, K = 856, F = 264 12.8, 9.1 (10.5); T = 20, K = 776,
+//     F = 5120 13.9, 11.1 (13.5); T = 120, K = 704, F = 4096 18.3, 19.3; T = 128,
+//     K = 776, F = 5440 20.0, 21.4; where three exceed a round, two are 4-8% slower than
+//     one (T = 20, K = 776, F = 8192).
+//   K = 897 to 1024, splits of 256 rows: T = 63, K = 1000, F = 496 13.3, 11.0 (15.0);
+//     T = 64, K = 1024, F = 4096 14.4, 14.7; T = 120, K = 1024, F = 2048 18.5, 20.2.
+//   K = 1025 to 1408, splits of 384 rows and more: T = 56, K = 1288, F = 4096 18.0,
+//     14.7 (20.5); T = 120, K = 1288, F = 4096 24.2, 21.6 (29.1); T = 128, K = 1160,
+//     F = 4096 21.4, 22.3.
+//   Longer K: T = 69, K = 6888, F = 544 11 splits of 640 rows 20.7, 27 of 256 25.0.
+int stream_min_k_tiles(int wm, int M, int N, int K, bool gate_up)
+{
+    if (wm == 4)
+        return 2;
+    const int ktiles = (int)cdiv(K, 128), tiles = (int)cdiv(M, 64);
+    if (!gate_up || ktiles < 5 || ktiles > 11)
+        return 4;
+    const bool wide = N > 96; // twice the exchange of 64 tokens
+    switch (ktiles) {
+    case 5: return wide && tiles > 2 && tiles <= 16 ? 2 : 4;
+    case 6: return 3 * tiles <= (wide ? kBlockTarget / 2 : kBlockTarget) ? 2 : 4;
+    case 7: return 3 * tiles <= (wide ? kBlockTarget * 3 / 4 : kBlockTarget) ? 2 : 4;
+    case 8: return 4 * tiles <= (wide ? kBlockTarget / 4 : kBlockTarget / 2) ? 2 : 4;
+    default: return 3 * tiles <= (!wide ? kBlockTarget : ktiles == 11 ? kBlockTarget * 3 / 4 : kBlockTarget / 2) ? 3 : 4;
+    }
+}
+
 void stream_step(Step &s, int wm, int M, int N, int K, bool gate_up)
 {
     s.stream_wm = wm;
     s.N = N;
+    const int min_k_tiles = stream_min_k_tiles(wm, M, N, K, gate_up);
     with_stream_tile(s, [&](auto tn, auto w) {
         constexpr int TN = decltype(tn)::value, WM = decltype(w)::value;
-        const int ktiles = (int)cdiv(K, 128);
-        const int min_k_tiles = WM == 4 ? 2 : !gate_up || ktiles <= 4 || ktiles > 11 ? 4 : ktiles <= 8 ? 2 : 3;
         if (gate_up)
             gemm_step<StreamGateUp<TN, WM>>(s, K_STREAM_GU, M, N, K, 2, true, 1, min_k_tiles);
         else

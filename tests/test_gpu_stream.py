@@ -88,7 +88,8 @@ def test_stream_variants(orc, T, variant):
     D, F = 520, 1032
     X, Wg, Wu, Wd = I.generate(T, D, F, seed=T)
     args = [gmlp.from_bf16_bits(a) for a in (X, Wg, Wu, Wd)]
-    assert all(_is_stream(line) for line in gmlp.describe(T, D, F))
+    # (128 tokens over 520 rows: the gate/up step runs on the ring, which is faster there.)
+    assert [_is_stream(line) for line in gmlp.describe(T, D, F)] == [T != 128, True]
     y = gmlp.forward(*args, workspace=gmlp.Workspace(T, D, F), **variant)
     torch.cuda.synchronize()
     _check(_f64(y), orc.gated_mlp_rows(X, Wg, Wu, Wd, **variant), "T=%d %s" % (T, variant))
