@@ -68,7 +68,8 @@ RAGGED = [
     (7, 256, 1032), (8, 264, 264), (9, 256, 512), (15, 264, 520), (16, 520, 1032),
     (17, 520, 1032), (33, 72, 136), (127, 256, 520), (128, 264, 1032), (129, 520, 264),
     (255, 256, 264), (257, 264, 520), (300, 1032, 2056),
-    # 32-, 64- and 96-token tiles (T <= 32, T <= 64, T <= 96), at their edges.
+    # The streaming tiles' token counts (the 32-, 64- and 96-token ring tiles at
+    # their edges are in test_gpu_ring.py).
     (32, 264, 1032), (48, 4104, 2056), (64, 520, 264), (65, 264, 520), (80, 1032, 264),
     (96, 264, 1032), (97, 520, 264),
 ]
@@ -91,8 +92,8 @@ def test_hidden_activations_past_2_gib(orc):
 
 
 def _random_shapes(n, seed):
-    # Token counts over every plan (GEMV, 32/64/96/128-token tiles, two token
-    # tiles, 256-token tiles), D and F multiples of 8 up to 2056.
+    # Token counts over the plans of the automatic path (GEMV, streaming tiles, two
+    # token tiles, 256-token tiles), D and F multiples of 8 up to 2056.
     r = np.random.default_rng(seed)
     t_choices = [1, 2, 3, 4, 5, 6, 7, 8, 9, 31, 32, 33, 64, 65, 96, 97, 127, 128, 129, 200, 256, 257, 384, 600]
     return [(int(r.choice(t_choices)), 8 * int(r.integers(1, 258)), 8 * int(r.integers(1, 258)))

@@ -77,7 +77,8 @@ def test_tiny_workload(sorc):
 
 # Ragged shapes (K, N multiples of 8 only), every row-kernel width (K up to
 # 512 columns per chunk-per-lane step: 1, 2, 4, 8, 16 chunks, and K > 8192
-# streamed in two passes), both matmul paths and both MFMA tile sizes.
+# streamed in two passes), on the GEMV, streaming and (above 128 rows) ring
+# kernels of the automatic path; test_gpu_ring.py has the ring's smaller tiles.
 SHAPES = [
     (1, 8, 8), (1, 264, 520), (2, 1000, 264), (3, 520, 1032), (5, 2056, 72), (8, 4104, 264),
     (9, 136, 264), (16, 256, 512), (33, 1032, 136), (64, 8192, 264), (127, 520, 1032),
