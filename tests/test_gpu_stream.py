@@ -95,6 +95,48 @@ def test_stream_variants(orc, T, variant):
     _check(_f64(y), orc.gated_mlp_rows(X, Wg, Wu, Wd, **variant), "T=%d %s" % (T, variant))
 
 
+# The options where test_stream_variants does not reach: the 128-column gate/up
+# tile (up to 16 tokens, weights above 2^22), and the epilogue after the split-K
+# exchange of every tile.
+@pytest.mark.parametrize("T,D,F,columns,splits", [(16, 2056, 3080, 128, 6), (9, 1032, 4104, 128, 3), (30, 1288, 1544, 64, 3),
+                                                  (60, 1032, 2056, 64, 3), (90, 2056, 1544, 64, 4),
+                                                  (100, 2056, 1544, 64, 4), (128, 1544, 4168, 64, 3)])
+@pytest.mark.parametrize("variant", [dict(rmsnorm=True, eps=1e-5), dict(activation="swish", beta=1.702, rmsnorm=True),
+                                     dict(activation="sigmoid")], ids=["rmsnorm", "rmsnorm_swiglu", "glu"])
+def test_stream_variants_after_the_exchange(orc, T, D, F, columns, splits, variant):
+    name, grid, _, got = gmlp.describe(T, D, F)[0]
+    tile = "GemmShape<2, 4, 1, 1, 1, 1, 128>" if columns == 128 else "GemmShape<2, 2, 1, 1, %d, 2, 128>" % -(-T // 32)
+    assert tile in name and got == splits and grid == -(-F // columns) * splits, (name, grid, got)
+    X, Wg, Wu, Wd = I.generate(T, D, F, seed=T + F)
+    h = gmlp.gate_up(*(gmlp.from_bf16_bits(a) for a in (X, Wg, Wu)), workspace=gmlp.Workspace(T, D, F), **variant)
+    torch.cuda.synchronize()
+    rows = np.arange(T) if T <= 16 else np.unique(np.concatenate([I.sample_rows(T, 24), np.arange(T - 2, T)]))
+    _, ref = orc.gated_mlp_rows(X, Wg, Wu, Wd, rows=rows, return_h=True, **variant)
+    _check(_f64(h)[rows], ref, "T=%d D=%d F=%d %s" % (T, D, F, variant))
+
+
+# The streaming tiles as the rest of a token split of the gate/up step: their
+# rows start past the whole tiles' in X, H and the row scales.
+@pytest.mark.parametrize("T,D,F", [(560, 1032, 12288), (530, 264, 12280), (1600, 2048, 8192)])
+def test_stream_rest_of_a_token_split(orc, T, D, F):
+    plan = gmlp.describe(T, D, F)
+    assert len(plan) == 3 and _is_stream(plan[1]) and ", 0, true, true>" in plan[1][0], plan
+    variant = dict(activation="swish", beta=1.702, rmsnorm=True, eps=1e-5)
+    X, Wg, Wu, Wd = I.generate(T, D, F, seed=T + F)
+    x, wg, wu, wd = (gmlp.from_bf16_bits(a) for a in (X, Wg, Wu, Wd))
+    ws = gmlp.Workspace(T, D, F)
+    h = torch.full((T, F), float("nan"), dtype=torch.bfloat16, device="cuda")
+    gmlp.gate_up(x, wg, wu, out=h, workspace=ws, **variant)
+    y = gmlp.forward(x, wg, wu, wd, workspace=ws, **variant)
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(h).all())  # every element written
+    first = T // 256 * 256
+    rows = np.unique(np.concatenate([I.sample_rows(T, 8), np.arange(first - 2, first + 6), np.arange(T - 4, T)]))
+    Y_ref, H_ref = orc.gated_mlp_rows(X, Wg, Wu, Wd, rows=rows, return_h=True, **variant)
+    _check(_f64(h)[rows], H_ref, "H T=%d D=%d F=%d" % (T, D, F))
+    _check(_f64(y)[rows], Y_ref, "Y T=%d D=%d F=%d" % (T, D, F))
+
+
 @pytest.mark.parametrize("M,K,N", [(9, 520, 264), (33, 1032, 72), (100, 2056, 1032), (16, 4104, 1544), (128, 72, 520)])
 def test_stream_softmax_matmul(M, K, N):
     assert _is_stream(smm.describe(M, K, N)[1])
