@@ -20,10 +20,15 @@ def test_splits(T, D, F, gu, dn):
 
 @pytest.mark.parametrize("T", [129, 160, 192, 193, 256, 300, 500, 1000])
 @pytest.mark.parametrize("D,F", [(8, 8), (72, 2056), (264, 520), (1032, 4104), (2048, 8192), (4096, 14336)])
-def test_splits_cover_k_and_fit_a_round(T, D, F):
-    for (name, grid, _, splits), K in zip(gmlp.describe(T, D, F), (D, F)):
-        assert 1 <= splits <= -(-K // 64)
-        assert splits == 1 or grid <= 256 or "false>" in name
+def test_splits_fit_a_round(T, D, F):
+    # (None of these plans has split tail tiles.)
+    for (name, grid, _, splits), M, K in zip(gmlp.describe(T, D, F), (F, D), (D, F)):
+        wm, wn, tm, tn, _, bk = [int(v) for v in name.split("GemmShape<")[1].split(">")[0].split(",")][1:7]
+        tiles = -(-M // (32 * wm * tm)) * -(-T // (32 * wn * tn))
+        pair = name.endswith(", 2, true, true>")  # a G and a U block per tile, each over all of K
+        assert grid == tiles * splits, (name, grid, splits)
+        assert splits == 1 or grid <= 256, (name, grid, splits)
+        assert splits == 2 if pair else 1 <= splits <= max(1, -(-K // bk) // 2), (name, splits)
 
 
 # Down steps of 257 to 384 tokens and 64 to 128 192-token tiles: where K is
