@@ -29,10 +29,10 @@
 //     what 128 read, which is what the narrow tiles are for.
 //
 // Measured over rotated weights, LDS ring against this (us, gate/up and down):
-// D = 1024, F = 4096, T = 48: 20.8 + 25.8 -> 12.5 + 10.7; D = 2048, F = 8192,
-// T = 51: 24.1 + 21.8 -> 22.4 + 15.6, of which the weight stream takes 15.4 +
+// D = 1024, F = 4096, T = 48: 21.1 + 26.5 -> 12.2 + 10.3; D = 2048, F = 8192,
+// T = 51: 24.5 + 22.3 -> 22.2 + 16.0, of which the weight stream takes 15.4 +
 // 10.3 (4.4 and 3.3 TB/s, launch included), the sum over the waves 3.0 + 2.0 and
-// the exchange 3.9 + 3.4.
+// the exchange the rest.
 #pragma once
 
 #include <type_traits>

@@ -252,14 +252,14 @@ double split_time(int64_t ktiles, int64_t splits, int64_t tiles, size_t stage_by
 }
 
 // Splits of K above 128 tokens: the count up to that of choose_splits with the
-// least estimated time.
-// Splitting to fill the chip whatever K is, as few as two k-tiles per split,
-// spent most of a small step in the exchange.  Measured, before and after, us:
-// down T = 328, D = 880, F = 2296 20.1 -> 15.4 (12 splits to 4); the whole MLP
-// T = 140, D = 1024, F = 4096 88.6 -> 41.2, T = 3839, D = 256, F = 512 39.8 -> 22.7,
-// T = 1505, D = 256, F = 512 25.6 -> 17.7.  Where K is long the count stays (T = 222,
-// D = 4096, F = 16384: 4 splits of the down step).  The 256-column down tiles,
-// which are chosen by the length of their splits, keep the other rule.
+// least estimated time.  Splitting to fill the chip whatever K is, as few as two
+// k-tiles per split, spent most of a small step in the exchange.  Measured,
+// before and after, us: down T = 328, D = 880, F = 2296 20.1 -> 15.4 (12 splits to
+// 4); the whole MLP T = 140, D = 1024, F = 4096 88.6 -> 41.2, T = 3839, D = 256,
+// F = 512 39.8 -> 22.7, T = 1505, D = 256, F = 512 25.6 -> 17.7.  Where K is long the
+// count stays (T = 222, D = 4096, F = 16384: 4 splits of the down step).  The
+// 256-column down tiles, which are chosen by the length of their splits, keep
+// the other rule.
 void choose_splits_by_time(Step &s, int tiles, int target, int tile_k, size_t stage_bytes, size_t tile_bytes)
 {
     const int64_t ktiles = cdiv(s.K, tile_k);
@@ -433,18 +433,23 @@ bool stream_slower(int64_t n, int64_t M, int64_t K, bool gate_up)
 // less with 64-column tiles.  With large weights the 64-column tiles' 128-byte
 // row segments stream at 5.5 TB/s against 6.4, and the token fragments, which
 // the streaming kernel reads 16 rows at a time, cost more than the ring's
-// rows (T = 128 at D = 4096, F = 14336: gate/up 80 us against 57.7).
+// rows (T = 128 at D = 4096, F = 14336: gate/up 56.3 us on the ring, 82.8).
 // Measured, ring against streaming, us:
-//   down     D = 1024, F = 4096: T = 8 21.9 -> 9.6, 48 25.8 -> 10.7, 128 32.7 ->
-//            18.6; D = 2048, F = 8192: T = 24 18.5 -> 13.0, 51 21.8 -> 15.6,
-//            128 27.8 -> 25.0; D = 3072, F = 8192: T = 96 23.9 -> 25.6 (kept)
-//   gate/up  D = 1024, F = 4096: T = 8 15.5 -> 10.6, 48 20.8 -> 12.5, 128 30.2 ->
-//            19.7; D = 2048, F = 8192: T = 51 24.1 -> 22.4, 128 31.6 -> 29.0;
-//            D = 3072, F = 8192: T = 64 29.2 -> 29.6 (kept)
+//   down     D = 1024, F = 4096: T = 8 22.6 -> 8.0, 48 25.4 -> 10.3, 128 33.3 ->
+//            17.9; D = 2048, F = 8192: T = 24 19.2 -> 12.5, 51 22.3 -> 16.0,
+//            128 28.7 -> 25.3; D = 3072, F = 8192: T = 96 24.4 -> 25.4 (kept)
+//   gate/up  D = 1024, F = 4096: T = 8 15.8 -> 9.5, 48 21.1 -> 12.2, 128 30.1 ->
+//            19.7; D = 2048, F = 8192: T = 51 24.5 -> 22.2, 128 32.7 -> 30.6;
+//            D = 3072, F = 8192: T = 64 30.1 -> 30.3 (kept)
+// The line at 2^24 from 110 drawn shapes of 17 to 128 tokens, streaming over ring,
+// mean and range over the shapes: 2^23 to 2^24 gate/up 0.85 (0.64-1.16), down 0.73
+// (0.53-0.98); 2^24 to 1.5 * 2^24 0.98 (0.76-1.28) and 0.94 (0.57-1.25), as often
+// slower as faster at any token count; from there to 2^25.5 1.19 (0.88-1.58) and 1.17
+// (0.95-1.44).
 // Up to 16 tokens the 128-column tiles also beat the ring at larger weights:
-// down D = 2048, F = 8192 18.4 -> 12.8, D = 3072, F = 8192 17.9 -> 14.5,
-// D = 4096, F = 14336 25.8 -> 23.8, D = 8192, F = 28672 82.7 -> 82.0 (kept);
-// gate/up 20.9 -> 18.0, 25.4 -> 23.3, D = 4096, F = 11008 35.6 -> 35.7 (kept).
+// down D = 2048, F = 8192 18.9 -> 13.3, D = 3072, F = 8192 18.5 -> 14.6,
+// D = 4096, F = 14336 27.1 -> 24.3, D = 8192, F = 28672 84.1 -> 82.7 (kept);
+// gate/up 21.1 -> 18.2, 25.9 -> 23.4, D = 4096, F = 11008 37.1 -> 36.5 (kept).
 // Gate/up steps of more than 96 128-column tiles keep the ring (pairs above
 // 64 tokens): they fill the chip without splits shorter than half of K.
 int stream_width(int64_t n, int64_t M, int64_t K, bool gate_up)
@@ -745,8 +750,9 @@ Plan make_plan(int64_t T, int64_t D, int64_t F, int path)
     // T = 320 221.9 -> 195.0 (75%); slower at equal work (D = 5120,
     // F = 13824, T = 300: 69.5 -> 74.7) and with 32 tiles (D = 2048,
     // F = 8192, T = 300: 27.5 -> 34.4).  The work alone does not tell where K
-    // is short: such steps are not split, and then the 128-token tiles have
-    // a third less of it on more CUs.
+    // is short: such steps are hardly split, and then the 128-token tiles have
+    // a third less of it on more CUs (T = 257, D = 4096, F = 1024 16.8 -> 13.6
+    // us, T = 300, F = 2048 21.8 -> 19.8; D = 8192, F = 768 14.9 -> 12.3).
     const int64_t down192 = cdiv(T, DownMid192::BN) * cdiv(D, DownMid192::BMW);
     if (T > 256 && T <= 2 * DownMid192::BN && down192 >= 64 && down192 <= kBlockTarget / 2) {
         Step mid;
