@@ -157,7 +157,7 @@ def _empty(shape, dtype, device, stream=None) -> torch.Tensor:
 # torch.cuda.stream(stream) that stream's.  A call's scratch is memory of this
 # device whichever one the arguments are on, since only the call's own stream
 # orders the reuse of the memory after the call.
-_CALL_DEVICE = "cuda"
+_CALL_DEVICE = torch.device("cuda")
 
 
 def _scratch(nbytes: int, rows: int, device, stream, plain: bool, invalid: str):
