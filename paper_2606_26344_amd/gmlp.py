@@ -149,6 +149,8 @@ def _empty(shape, dtype, device, stream=None) -> torch.Tensor:
     there while the kernels still write to it."""
     if stream is None:
         return torch.empty(shape, dtype=dtype, device=device)
+    if not isinstance(stream, torch.cuda.Stream):  # calls need its cuda_stream only
+        stream = torch.cuda.ExternalStream(stream.cuda_stream)
     with torch.cuda.stream(stream):
         return torch.empty(shape, dtype=dtype, device=device)
 

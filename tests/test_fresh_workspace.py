@@ -117,6 +117,31 @@ def test_calls_without_a_workspace_are_captured():
         assert np.array_equal(gmlp.to_bf16_bits(z), gmlp.to_bf16_bits(want_z))
 
 
+@pytest.mark.gpu
+def test_a_stream_known_by_its_handle_only():
+    # All that a call asks of a stream is its cuda_stream, also where it takes
+    # scratch memory (which it takes on that stream).
+    class Handle:
+        def __init__(self, stream):
+            self.cuda_stream = stream.cuda_stream
+
+    side = torch.cuda.Stream()
+    x, wg, wu, wd = (gmlp.from_bf16_bits(a) for a in I.generate(100, 2056, 1544, seed=1))
+    want = gmlp.forward(x, wg, wu, wd)
+    torch.cuda.synchronize()
+    before = torch.cuda.current_stream()
+    y, h, d = torch.empty_like(want), torch.empty(100, 1544, dtype=torch.bfloat16, device="cuda"), torch.empty_like(want)
+    gmlp.forward(x, wg, wu, wd, out=y, stream=Handle(side))
+    gmlp.gate_up(x, wg, wu, out=h, stream=Handle(side))
+    gmlp.down(h, wd, out=d, stream=Handle(side))
+    z = smm.softmax_matmul(x, wg, stream=Handle(side))
+    torch.cuda.synchronize()
+    assert torch.cuda.current_stream() == before
+    for got in (y, d):
+        assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+    assert torch.equal(z.view(torch.int16), smm.softmax_matmul(x, wg).view(torch.int16))
+
+
 def test_a_refused_shape_is_reported_as_before():
     # No device needed: the shape is refused before anything is allocated.
     assert gmlp._scratch(0, 4, "cuda", None, True, "unused") == (None, None)
