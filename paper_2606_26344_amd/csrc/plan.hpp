@@ -400,8 +400,8 @@ constexpr int kStreamWideTokens = 16; // the 128-column tiles: one 16-token tile
 //     block each, where the ring's 128-column tiles split K two or three ways,
 //     which tells where K is long.  Gate/up T = 120, F = 8704: K = 904 24.5 -> 24.0,
 //     1200 26.4 -> 27.9, 1920 29.2 -> 39.5; T = 80: K = 1360 26.1 -> 25.1, 1600 26.8 ->
-//     28.1; T = 50, F = 9216: K = 1400 22.4 -> 24.0.  Down T = 48, D = 9216: K = 1200 13.9 -> 13.1, 1400 14.4 -> 14.8,
-//     1600 14.6 -> 16.1.  From 76 ring tiles on (9600 columns) its three splits
+//     28.1; T = 50, F = 9216: K = 1400 22.4 -> 24.0.  Down T = 48, D = 9216: K = 1200
+//     13.9 -> 13.1, 1400 14.4 -> 14.8, 1600 14.6 -> 16.1.  From 76 ring tiles on (9600 columns) its three splits
 //     fill the chip and gain less: down T = 48, D = 10240, K = 1504 15.6 -> 14.5.
 //   * down steps of 16385 to 32768 columns, more than one round of 64-column
 //     tiles and one of 128-column tiles: T = 20, D = 20480 K = 136 5.9 -> 5.0,
@@ -485,8 +485,8 @@ auto with_stream_tile(const Step &s, F f)
 // weights a wave, feels while its blocks are few; above 96 tokens, where a split
 // adds 64 KB a tile to the exchange, these have to be fewer.  Unsplit or in splits
 // of 512 rows and so, us, with the ring's time:
-//   K = 577 to 640, two splits: T = 128, K = 600, F = 264 17.6, 16.4 (16.9); F = 2048
-//     16.9, 17.4; up to 64 tokens no gain.
+//   K = 577 to 640, two splits: T = 128, K = 600, F = 264 17.6, 16.4 (16.9); T = 120,
+//     K = 520, F = 2048 15.9, 16.6 (15.5); up to 64 tokens no gain.
 //   K = 641 to 896, three: T = 31, K = 856, F = 264 12.8, 9.1 (10.5); T = 20, K = 776,
 //     F = 5120 13.9, 11.1 (13.5); T = 120, K = 704, F = 4096 18.3, 19.3; T = 128,
 //     K = 776, F = 5440 20.0, 21.4; where three exceed a round, two are 4-8% slower than
